@@ -973,6 +973,8 @@ struct cfd_batch {
   bool one_sided = false;  // some block has faces with the one-sided viscous closure
   // work lists
   TileList visc_tl{};
+  bool visc_small = false;      // tile shape and planes per tile of the prepass (visc_plan)
+  int visc_kc[kMaxBlocks] = {};
   TileList sweep_tl[3]{};
   int cfg[3] = {0, 0, 0};       // tile configuration per direction
   int persist[3] = {0, 0, 0};   // persistent schedule per direction
@@ -1015,11 +1017,11 @@ void fill_tiles(cfd_batch* bt) {
   const int nb = (int)bt->blocks.size();
   bt->visc_tl.nblk = nb;
   bt->visc_tl.prefix[0] = 0;
-  for (int b = 0; b < nb; ++b) {
-    int kc, t;
-    visc_tiling(bt->blocks[b]->g, kViscMinTilesBatch, &kc, &t);
-    bt->visc_tl.prefix[b + 1] = bt->visc_tl.prefix[b] + t;
-  }
+  Geom gs[kMaxBlocks];
+  int tiles[kMaxBlocks];
+  for (int b = 0; b < nb; ++b) gs[b] = bt->blocks[b]->g;
+  visc_plan(gs, nb, true, bt->precision == CFD_FP64, &bt->visc_small, bt->visc_kc, tiles);
+  for (int b = 0; b < nb; ++b) bt->visc_tl.prefix[b + 1] = bt->visc_tl.prefix[b] + tiles[b];
   for (int d = 0; d < 3; ++d) {
     TileList& tl = bt->sweep_tl[d];
     tl.nblk = nb;
@@ -1134,8 +1136,7 @@ void build_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* con
       v.vis = B->vis;
       v.ph = ph;
       v.one_sided = one_sided_mask(B->d);
-      int tiles;
-      visc_tiling(B->g, kViscMinTilesBatch, &v.kc, &tiles);
+      v.kc = bt->visc_kc[b];
       for (int d = 0; d < 3; ++d) {
         SweepBlock& a = sa[(st * 3 + d) * nb + b];
         std::memset(&a, 0, sizeof a);
@@ -1174,8 +1175,8 @@ hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
   hipError_t e = hipSuccess;
   if (bt->viscous) {
     const ViscArgs* va = bt->visc_args_dev + st * nb;
-    e = bt->precision == CFD_FP64 ? launch_visc_batch<double>(va, bt->visc_tl, bt->one_sided, bt->stream)
-                                  : launch_visc_batch<float>(va, bt->visc_tl, bt->one_sided, bt->stream);
+    e = bt->precision == CFD_FP64 ? launch_visc_batch<double>(va, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream)
+                                  : launch_visc_batch<float>(va, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream);
     if (e != hipSuccess) return e;
     PtrTable t;
     std::memset(&t, 0, sizeof t);
@@ -1233,8 +1234,8 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
     rc = upload_args(bt, Qn, QA, QB, dt_dev);
     if (rc == CFD_OK) {
       hipError_t e = bt->precision == CFD_FP64
-                         ? launch_visc_batch<double>(bt->visc_args_dev, bt->visc_tl, bt->one_sided, bt->stream)
-                         : launch_visc_batch<float>(bt->visc_args_dev, bt->visc_tl, bt->one_sided, bt->stream);
+                         ? launch_visc_batch<double>(bt->visc_args_dev, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream)
+                         : launch_visc_batch<float>(bt->visc_args_dev, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream);
       if (e != hipSuccess) rc = hip_fail(e, "tuning prepass");
     }
   }

@@ -125,13 +125,30 @@ hipError_t launch_metrics(const MetricArgs& a, hipStream_t s) {
 // formed about twice per chunk instead of at each of its eighteen stencil uses, and Q is
 // read once per column.
 // =====================================================================================
-constexpr int VI = 64, VJ = 16, VNT = VI * VJ;
-constexpr int kViscChunk = 128;    // most planes per workgroup (fewer when nk is smaller)
-constexpr int kViscMinTiles = 256;  // workgroups a single-block launch aims for (one per CU)
+constexpr int kViscChunk = 128;  // most planes per workgroup (fewer when nk is smaller)
 
-template <typename R>
+// Two tile shapes.  64 x 16 columns (1024 threads, one workgroup per CU) read the fewest halo
+// nodes of Q per output and stream a large block at the copy rate; 32 x 8 (256 threads, four
+// workgroups per CU) suit blocks whose Q stays in the 256 MB last-level cache, where the wider
+// halo costs little and finer, independently waiting workgroups fill the chip.  FP64 prepass,
+// 64 x 16 against 32 x 8, each at its best chunk: 32^3 11.1 / 7.4 us, 96x80x72 33.9 / 28.7,
+// 160^3 189 / 172, 192x112x72 74 / 68, 190x131x93 114 / 112, 256^3 755 / 793; FP32: 32^3
+// 8.9 / 7.5, 96x80x72 22.3 / 21.2, 160^3 130 / 124, 192x112x72 50.6 / 51.4, 190x131x93
+// 76 / 83, 256^3 521 / 596.  The lines lie between: 6M points in FP64, 1M in FP32.
+template <bool SMALL>
+struct ViscTile {
+  static constexpr int VI = SMALL ? 32 : 64, VJ = SMALL ? 8 : 16, NT = VI * VJ;
+  static constexpr int NHALO = 6 * (VI + VJ);  // halo nodes of a plane (a cross, no corners)
+  static constexpr int NBUF = SMALL ? 2 : 1;   // LDS planes: two need one barrier per plane
+  static constexpr int SLOTS = SMALL ? 1024 : 256;  // workgroups the chip holds at once
+  static_assert(NHALO <= NT, "one halo node per thread");
+};
+constexpr int64_t kViscSmallFp64 = 6000000, kViscSmallFp32 = 1000000;
+
+template <typename R, bool SMALL>
 struct ViscShared {
-  R p[4][VJ + 6][VI + 6];  // (u, v, w, T) of plane k at (j - j0 + 3, i - i0 + 3)
+  // (u, v, w, T) of plane k at (j - j0 + 3, i - i0 + 3)
+  R p[ViscTile<SMALL>::NBUF][4][ViscTile<SMALL>::VJ + 6][ViscTile<SMALL>::VI + 6];
 };
 
 template <typename R>
@@ -193,8 +210,9 @@ __device__ __forceinline__ R grad6(F g) {
 
 // OS: the block may have faces with the one-sided closure (a separate instantiation, so
 // that blocks without them keep the register budget of the plain prepass)
-template <typename R, bool OS>
-__device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R>& sh) {
+template <typename R, bool OS, bool SMALL>
+__device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R, SMALL>& sh) {
+  constexpr int VI = ViscTile<SMALL>::VI, VJ = ViscTile<SMALL>::VJ, NBUF = ViscTile<SMALL>::NBUF;
   const Geom& g = a.g;
   const int nti = (g.ni + VI - 1) / VI, ntj = (g.nj + VJ - 1) / VJ;
   const int i0 = (t % nti) * VI, j0 = ((t / nti) % ntj) * VJ;
@@ -235,23 +253,24 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
   }
   for (int k = k0; k < k1; ++k) {
     if (own) primitives<R>(Q, plane, pc + (uint32_t)(k + 3) * sk, gg, P[6]);
+    auto& sp = sh.p[NBUF == 2 ? (k & 1) : 0];
     if (own) {
 #pragma unroll
-      for (int n = 0; n < 4; ++n) sh.p[n][tj + 3][ti + 3] = P[3][n];
+      for (int n = 0; n < 4; ++n) sp[n][tj + 3][ti + 3] = P[3][n];
     }
     if (hval) {
       R ph4[4];
       primitives<R>(Q, plane, ph + (uint32_t)k * sk, gg, ph4);
 #pragma unroll
-      for (int n = 0; n < 4; ++n) sh.p[n][hj - j0 + 3][hi - i0 + 3] = ph4[n];
+      for (int n = 0; n < 4; ++n) sp[n][hj - j0 + 3][hi - i0 + 3] = ph4[n];
     }
     __syncthreads();
     if (act) {
       R gr[4][3];  // d(u, v, w, T)/d(xi, eta, zeta)
 #pragma unroll
       for (int n = 0; n < 4; ++n) {
-        gr[n][0] = grad6<R>([&](int m) { return sh.p[n][tj + 3][ti + 3 + m]; });
-        gr[n][1] = grad6<R>([&](int m) { return sh.p[n][tj + 3 + m][ti + 3]; });
+        gr[n][0] = grad6<R>([&](int m) { return sp[n][tj + 3][ti + 3 + m]; });
+        gr[n][1] = grad6<R>([&](int m) { return sp[n][tj + 3 + m][ti + 3]; });
         gr[n][2] = grad6<R>([&](int m) { return P[3 + m][n]; });
       }
       const uint32_t p = pc + (uint32_t)k * sk;
@@ -333,14 +352,16 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
     for (int m = 0; m < 6; ++m)
 #pragma unroll
       for (int n = 0; n < 4; ++n) P[m][n] = P[m + 1][n];
-    __syncthreads();  // plane k of the LDS tile is consumed
+    // plane k of the LDS tile is consumed; with two buffers the next plane goes to the other
+    // one, and the barrier of the plane after next orders that write behind these reads
+    if constexpr (NBUF == 1) __syncthreads();
   }
 }
 
-template <typename R, bool OS>
-__global__ __launch_bounds__(VNT) __attribute__((amdgpu_waves_per_eu(4))) void k_visc(ViscArgs a) {
-  __shared__ ViscShared<R> sh;
-  visc_tile<R, OS>(a, xcd_remap(blockIdx.x, gridDim.x), sh);
+template <typename R, bool OS, bool SMALL>
+__global__ __launch_bounds__(ViscTile<SMALL>::NT) __attribute__((amdgpu_waves_per_eu(4))) void k_visc(ViscArgs a) {
+  __shared__ ViscShared<R, SMALL> sh;
+  visc_tile<R, OS, SMALL>(a, xcd_remap(blockIdx.x, gridDim.x), sh);
 }
 
 __global__ __launch_bounds__(256) void k_round(const double* __restrict__ src, float* __restrict__ dst, int64_t n) {
@@ -381,53 +402,102 @@ hipError_t launch_half_metrics(const Geom& g, const double* met, float* hm, hipS
   return hipGetLastError();
 }
 
-// chunk length and tile count of one block (i-tile fastest, then j-tile, then k-chunk):
-// at most kViscChunk planes per tile, that bound halved (down to 8) while the block would
-// give fewer than min_tiles workgroups, and nk split into the fewest chunks of equal length
-// under it; a longer chunk re-reads fewer priming planes, more tiles fill the chip
-void visc_tiling(const Geom& g, int min_tiles, int* kc, int* tiles) {
-  const int cols = ((g.ni + VI - 1) / VI) * ((g.nj + VJ - 1) / VJ);
-  int c = kViscChunk;
-  while (c > 8 && cols * ((g.nk + c - 1) / c) < min_tiles) c /= 2;
-  const int nch = (g.nk + c - 1) / c;
-  *kc = (g.nk + nch - 1) / nch;
-  *tiles = cols * ((g.nk + *kc - 1) / *kc);
+static int visc_cols(const Geom& g, bool small) {
+  const int vi = small ? ViscTile<true>::VI : ViscTile<false>::VI, vj = small ? ViscTile<true>::VJ : ViscTile<false>::VJ;
+  return ((g.ni + vi - 1) / vi) * ((g.nj + vj - 1) / vj);
+}
+
+// Tile shape, chunk lengths and tile counts of a launch over nb blocks (i-tile fastest, then
+// j-tile, then k-chunk).  One block, or a batch of blocks that take the small shape: the chunk
+// bound c (<= kViscChunk) with the least rounds x (c + 3), rounds the times the tiles fill the
+// chip and 3 the measured cost of the six priming planes of a chunk in units of an output
+// plane; nk is then split into the fewest equal chunks under c.  (160^3 FP64 before, with a
+// bound halved until 256 tiles were reached: 300 tiles of 1024 threads, two rounds, 258 us.)
+// A batch of large blocks has several rounds in any case and keeps chunks of at most
+// kViscChunk, halved (down to 8) where a block has fewer than kViscMinTilesBatch tiles.
+void visc_plan(const Geom* gs, int nb, bool batch, bool fp64, bool* small_out, int* kc, int* tiles) {
+  int64_t points = 0;
+  int nkmax = 0;
+  for (int b = 0; b < nb; ++b) {
+    points += (int64_t)gs[b].ni * gs[b].nj * gs[b].nk;
+    nkmax = gs[b].nk > nkmax ? gs[b].nk : nkmax;
+  }
+  const bool small = points < (fp64 ? kViscSmallFp64 : kViscSmallFp32);
+  *small_out = small;
+  int best = 0;
+  if (!batch || small) {
+    const int slots = small ? ViscTile<true>::SLOTS : ViscTile<false>::SLOTS;
+    int64_t best_cost = INT64_MAX;
+    for (int c = nkmax < kViscChunk ? nkmax : kViscChunk; c >= 1; --c) {
+      int64_t t = 0;
+      for (int b = 0; b < nb; ++b) t += (int64_t)visc_cols(gs[b], small) * ((gs[b].nk + c - 1) / c);
+      const int64_t cost = ((t + slots - 1) / slots) * (c + 3);
+      if (cost < best_cost) best_cost = cost, best = c;
+    }
+  }
+  for (int b = 0; b < nb; ++b) {
+    const int cols = visc_cols(gs[b], small), nk = gs[b].nk;
+    int c = best;
+    if (!c)
+      for (c = kViscChunk; c > 8 && cols * ((nk + c - 1) / c) < kViscMinTilesBatch;) c /= 2;
+    const int nch = (nk + c - 1) / c;
+    kc[b] = (nk + nch - 1) / nch;
+    tiles[b] = cols * ((nk + kc[b] - 1) / kc[b]);
+  }
 }
 
 // one workgroup per tile of the concatenated list (ids remapped XCD-contiguously)
-template <typename R, bool OS>
-__global__ __launch_bounds__(VNT) __attribute__((amdgpu_waves_per_eu(4))) void k_visc_batch(const ViscArgs* __restrict__ args, TileList tl) {
-  __shared__ ViscShared<R> sh;
+template <typename R, bool OS, bool SMALL>
+__global__ __launch_bounds__(ViscTile<SMALL>::NT) __attribute__((amdgpu_waves_per_eu(4))) void k_visc_batch(const ViscArgs* __restrict__ args, TileList tl) {
+  __shared__ ViscShared<R, SMALL> sh;
   const int t = xcd_remap(blockIdx.x, gridDim.x);
   int blk = 0;
   while (t >= tl.prefix[blk + 1]) ++blk;
-  visc_tile<R, OS>(args[blk], t - tl.prefix[blk], sh);
+  visc_tile<R, OS, SMALL>(args[blk], t - tl.prefix[blk], sh);
+}
+
+template <typename R, bool SMALL>
+static void launch_visc_shape(const ViscArgs& a, int tiles, hipStream_t s) {
+  if (a.one_sided)
+    hipLaunchKernelGGL((k_visc<R, true, SMALL>), dim3(tiles), dim3(ViscTile<SMALL>::NT), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_visc<R, false, SMALL>), dim3(tiles), dim3(ViscTile<SMALL>::NT), 0, s, a);
 }
 
 template <typename R>
 hipError_t launch_visc(ViscArgs a, hipStream_t s) {
   int tiles;
-  visc_tiling(a.g, kViscMinTiles, &a.kc, &tiles);
-  if (a.one_sided)
-    hipLaunchKernelGGL((k_visc<R, true>), dim3(tiles), dim3(VNT), 0, s, a);
+  bool small;
+  visc_plan(&a.g, 1, false, sizeof(R) == 8, &small, &a.kc, &tiles);
+  if (small)
+    launch_visc_shape<R, true>(a, tiles, s);
   else
-    hipLaunchKernelGGL((k_visc<R, false>), dim3(tiles), dim3(VNT), 0, s, a);
+    launch_visc_shape<R, false>(a, tiles, s);
   return hipGetLastError();
 }
 template hipError_t launch_visc<double>(ViscArgs, hipStream_t);
 template hipError_t launch_visc<float>(ViscArgs, hipStream_t);
 
-// args_dev[b].kc must be the chunk length visc_tiling gives for block b
-template <typename R>
-hipError_t launch_visc_batch(const ViscArgs* args_dev, const TileList& tl, bool one_sided, hipStream_t s) {
+template <typename R, bool SMALL>
+static void launch_visc_batch_shape(const ViscArgs* args_dev, const TileList& tl, bool one_sided, hipStream_t s) {
+  const dim3 grid(tl.prefix[tl.nblk]), wg(ViscTile<SMALL>::NT);
   if (one_sided)
-    hipLaunchKernelGGL((k_visc_batch<R, true>), dim3(tl.prefix[tl.nblk]), dim3(VNT), 0, s, args_dev, tl);
+    hipLaunchKernelGGL((k_visc_batch<R, true, SMALL>), grid, wg, 0, s, args_dev, tl);
   else
-    hipLaunchKernelGGL((k_visc_batch<R, false>), dim3(tl.prefix[tl.nblk]), dim3(VNT), 0, s, args_dev, tl);
+    hipLaunchKernelGGL((k_visc_batch<R, false, SMALL>), grid, wg, 0, s, args_dev, tl);
+}
+
+// small, args_dev[b].kc and the tile counts of tl must be those of visc_plan
+template <typename R>
+hipError_t launch_visc_batch(const ViscArgs* args_dev, const TileList& tl, bool small, bool one_sided, hipStream_t s) {
+  if (small)
+    launch_visc_batch_shape<R, true>(args_dev, tl, one_sided, s);
+  else
+    launch_visc_batch_shape<R, false>(args_dev, tl, one_sided, s);
   return hipGetLastError();
 }
-template hipError_t launch_visc_batch<double>(const ViscArgs*, const TileList&, bool, hipStream_t);
-template hipError_t launch_visc_batch<float>(const ViscArgs*, const TileList&, bool, hipStream_t);
+template hipError_t launch_visc_batch<double>(const ViscArgs*, const TileList&, bool, bool, hipStream_t);
+template hipError_t launch_visc_batch<float>(const ViscArgs*, const TileList&, bool, bool, hipStream_t);
 
 // =====================================================================================
 // Direction sweep: modified AFWENO inviscid derivative (Sec. 4.5.1, Figs 10-11, Eq 19),

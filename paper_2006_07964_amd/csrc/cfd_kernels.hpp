@@ -35,7 +35,7 @@ struct ViscArgs {
   const void* met_r;  // the 10 metric planes in the compute type
   void* vis;  // 12 planes of the compute type
   Phys ph;
-  int kc;     // planes per tile (set by visc_tiling)
+  int kc;     // planes per tile (set by visc_plan)
   int periodic;  // bit d: the block is periodic with itself along d, the kernel fills
                  // the direction-d flux halos across the d-faces
   int one_sided;  // bit 2*axis + side (side 1: high face): a physical face whose viscous
@@ -50,12 +50,13 @@ hipError_t launch_round(const double* src, float* dst, int64_t n, hipStream_t s)
 // direction d, component c of the direction-d metric at n+1/2 (sixth-order interpolation in
 // FP64, rounded once), for n = -1 .. nd-1 along d at every stored position across.
 hipError_t launch_half_metrics(const Geom& g, const double* met, float* hm, hipStream_t s);
-// batched viscous prepass over the tiles (64 x 16 columns, a chunk of k planes) of every
-// block; one_sided: some block has faces with the one-sided closure
+// batched viscous prepass over the tiles of every block; one_sided: some block has faces with
+// the one-sided closure
 template <typename R>
-hipError_t launch_visc_batch(const ViscArgs* args_dev, const TileList& tl, bool one_sided, hipStream_t s);
-void visc_tiling(const Geom& g, int min_tiles, int* kc, int* tiles);
-// the tiles each block of a batched prepass aims for: a block too small to give them with
+hipError_t launch_visc_batch(const ViscArgs* args_dev, const TileList& tl, bool small, bool one_sided, hipStream_t s);
+// tile shape (small: 32 x 8 columns, else 64 x 16), planes per tile and tiles of each block
+void visc_plan(const Geom* gs, int nb, bool batch, bool fp64, bool* small, int* kc, int* tiles);
+// the tiles each large block of a batched prepass aims for: a block too small to give them with
 // long chunks (the 24-block O-grid: 21 columns of 72-96 planes) is cut into chunks of 16
 // planes, which balances the launch over the CUs better than whole columns (1% faster step
 // in mixed precision, 1.5% in FP64, measured) despite 6 priming planes per chunk; large
