@@ -149,6 +149,7 @@ struct cfd_block {
   bool has_interface = false;
   int patched = 0;  // exchanges that connect part of one of its physical faces to a block
   int cfg[3] = {0, 0, 0};  // sweep tile shape per direction (set at creation)
+  bool own_tiles = false;  // the caller chose the shapes: every sweep runs them
   // small device scratch for reductions
   unsigned long long* red_dev = nullptr;
   int* flag_dev = nullptr;
@@ -501,8 +502,11 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     a.b.out = last ? out : nullptr;
     const char* name = (last && out_kind == kOutRK) ? kSweepRkNames[dirs[n]] : kSweepNames[dirs[n]];
     ProfScope ps(&b->prof, name, b->stream);
-    hipError_t e = b->d.precision == CFD_FP64 ? launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]])
-                                              : launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
+    hipError_t e = hipSuccess;
+    if (b->d.precision != CFD_FP64)
+      e = launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
+    else if (b->own_tiles || !launch_march(dirs[n], a, b->stream, &e))
+      e = launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
     ps.done();
     if (e != hipSuccess) return hip_fail(e, "sweep launch");
   }
@@ -1653,6 +1657,7 @@ int cfd_block_set_tiles(cfd_block* b, const int* cfg) {
   for (int d = 0; d < 3; ++d)
     if (cfg[d] < 0 || cfg[d] >= kTileCfgs) return fail(CFD_ERR_ARG, "tile configuration out of range");
   for (int d = 0; d < 3; ++d) b->cfg[d] = cfg[d];
+  b->own_tiles = true;
   return CFD_OK;
 }
 

@@ -373,6 +373,123 @@ __device__ __forceinline__ R weno_left(R a, R b, R c, R d, R e, R eps, bool line
   return (q0 * p0 + q1 * p1 + q2 * p2) * rcp(R(0.0625) * q0 + R(0.625) * q1 + R(0.3125) * q2);
 }
 
+// ---- the same reconstruction from first differences --------------------------------------
+// The characteristic space of a node for the marching sweep.  WENO weights need only the
+// differences of the projected values, and each interpolated value is the node's own plus a
+// combination of them, so four differences of Q are projected instead of five states, and
+// the state at the half point is the node's primitives plus an increment: its pressure and
+// velocities come without forming the conserved state (fewer FP64 instructions, and no
+// cancellation in the pressure).  The vectors k stay divided by rho (rk); the back-projection
+// carries the 1/8 of the correction form of weno_pair.
+template <typename R>
+struct NodeSpace {
+  R rkx, rky, rkz;          // k / rho
+  R u, v, w, p, ke, rho;
+  R rgc2;                   // rho (gamma-1) / c^2
+  R gpr;                    // (gamma-1) / (sqrt2 rho c)
+  R rho8, rr8, a8, b8;      // rho, rho^2, rho / (sqrt2 c) and rho c / sqrt2, each over 8
+};
+
+template <typename R>
+__device__ __forceinline__ NodeSpace<R> node_space(const R q[5], R mx, R my, R mz, const Gas<R>& G) {
+  NodeSpace<R> B;
+  const R s2 = R(0.70710678118654752440);  // 1/sqrt2
+  const R rinv = rcp(q[0]);
+  const R km = rsq(mx * mx + my * my + mz * mz) * rinv;
+  B.rkx = mx * km;
+  B.rky = my * km;
+  B.rkz = mz * km;
+  B.rho = q[0];
+  B.u = q[1] * rinv;
+  B.v = q[2] * rinv;
+  B.w = q[3] * rinv;
+  B.ke = R(0.5) * (B.u * B.u + B.v * B.v + B.w * B.w);
+  B.p = G.gm1 * (q[4] - B.rho * B.ke);
+  const R c2 = G.gamma * B.p * rinv;
+  const R cinv = rsq(c2);
+  const R rc = B.rho * cinv;
+  B.rgc2 = G.gm1 * cinv * rc;
+  B.gpr = (s2 * G.gm1) * cinv * rinv;
+  B.rho8 = R(0.125) * B.rho;
+  B.rr8 = B.rho8 * B.rho;
+  B.a8 = (R(0.125) * s2) * rc;
+  B.b8 = B.a8 * c2;
+  return B;
+}
+
+// L times a difference of conserved states (the formulas of project)
+template <typename R>
+__device__ __forceinline__ void project_diff(const NodeSpace<R>& B, const R x[5], R V[5]) {
+  const R s2 = R(0.70710678118654752440);
+  const R yu = x[1] - B.u * x[0], yv = x[2] - B.v * x[0], yw = x[3] - B.w * x[0];
+  const R pp = B.ke * x[0] - B.u * x[1] - B.v * x[2] - B.w * x[3] + x[4];
+  const R s = B.rho * x[0] - B.rgc2 * pp;
+  V[0] = B.rkx * s + (yv * B.rkz - yw * B.rky);
+  V[1] = B.rky * s + (yw * B.rkx - yu * B.rkz);
+  V[2] = B.rkz * s + (yu * B.rky - yv * B.rkx);
+  const R kd = B.rkx * yu + B.rky * yv + B.rkz * yw;
+  const R pr = pp * B.gpr;
+  V[3] = pr + s2 * kd;
+  V[4] = pr - s2 * kd;
+}
+
+// weno_pair's correction form from the first differences D1..D4 of the five values: eight
+// times the values at i+1/2 (cl) and i-1/2 (cr) minus the centre value; eps4 = 4 eps
+template <typename R>
+__device__ __forceinline__ void weno_diff(R D1, R D2, R D3, R D4, R eps4, R& cl, R& cr) {
+  const R d0 = D2 - D1, e0 = R(3) * D2 - D1;
+  const R d1 = D3 - D2, e1 = -(D2 + D3);
+  const R d2 = D4 - D3, e2 = D4 - R(3) * D3;
+  const R A0 = d0 + R(2) * e0, A1 = d1 - R(2) * e1, A2 = d2 - R(2) * e2;
+  const R B0 = d0 - R(2) * e0, B1 = d1 + R(2) * e1, B2 = d2 + R(2) * e2;
+  const R t0 = R(13.0 / 3.0) * d0 * d0 + (e0 * e0 + eps4);
+  const R t1 = R(13.0 / 3.0) * d1 * d1 + (e1 * e1 + eps4);
+  const R t2 = R(13.0 / 3.0) * d2 * d2 + (e2 * e2 + eps4);
+  const R s0 = t0 * t0, s1 = t1 * t1, s2 = t2 * t2;
+  const R q0 = s1 * s2, q1 = s0 * s2, q2 = s0 * s1;
+  const R t10 = R(10) * q1;
+  const R nl = q0 * A0 + t10 * A1 + R(5) * (q2 * A2);
+  const R nr = R(5) * (q0 * B0) + t10 * B1 + q2 * B2;
+  const R dl = q0 + t10 + R(5) * q2;
+  const R dr = R(5) * q0 + t10 + q2;
+  const R inv = rcp(dl * dr);
+  cl = nl * (dr * inv);
+  cr = nr * (dl * inv);
+}
+
+// Steger-Warming flux of one sign at a half point whose state is the node's plus R V / 8,
+// through the hatted metric (mx, my, mz) of magnitude mag = 1 / minv.  With du the velocity
+// increment, p = p_node + (rho c / sqrt2)(V3 + V4) / 8 - (gamma-1) rho |du|^2 / 2 exactly.
+template <int SIGN, typename R>
+__device__ __forceinline__ void half_flux(const NodeSpace<R>& B, const Gas<R>& G, const R V[5], R mx, R my, R mz, R mag,
+                                          R minv, R F[5]) {
+  const R sp = V[3] + V[4], sm = (V[3] - V[4]) * R(0.70710678118654752440);
+  const R kv = B.rkx * V[0] + B.rky * V[1] + B.rkz * V[2];
+  const R rho = B.rho8 * kv + (B.a8 * sp + B.rho);
+  const R rinv = rcp(rho);
+  const R g = B.rr8 * rinv;
+  const R du = g * (B.rky * V[2] - B.rkz * V[1] + B.rkx * sm);
+  const R dv = g * (B.rkz * V[0] - B.rkx * V[2] + B.rky * sm);
+  const R dw = g * (B.rkx * V[1] - B.rky * V[0] + B.rkz * sm);
+  const R u = B.u + du, v = B.v + dv, w = B.w + dw;
+  const R p = (B.b8 * sp + B.p) - (R(0.5) * G.gm1 * rho) * (du * du + dv * dv + dw * dw);
+  const R c2 = G.gamma * p * rinv;
+  const R c = c2 * rsq(c2);
+  const R ke = R(0.5) * (u * u + v * v + w * w);
+  const R mu = mx * u + my * v + mz * w;
+  const R l4 = mu + mag * c, l5 = mu - mag * c;
+  // twice the split eigenvalues; f carries the half
+  const R a1 = mu + R(SIGN) * fabs(mu), a4 = l4 + R(SIGN) * fabs(l4), a5 = l5 + R(SIGN) * fabs(l5);
+  const R f = rho * (R(0.5) * G.inv2g);
+  const R s45 = a4 + a5;
+  const R fd = f * ((a4 - a5) * (c * minv));
+  F[0] = f * ((R(2) * G.gm1) * a1 + s45);
+  F[1] = F[0] * u + fd * mx;
+  F[2] = F[0] * v + fd * my;
+  F[3] = F[0] * w + fd * mz;
+  F[4] = F[0] * ke + (f * s45) * (c2 * G.gm1inv) + fd * mu;
+}
+
 // ---- sixth-order half-point interpolation of node metrics ---------------------------
 // m(i+1/2) = (3 m(i-2) - 25 m(i-1) + 150 m(i) + 150 m(i+1) - 25 m(i+2) + 3 m(i+3)) / 256;
 // combined with Eq 19 it gives the sixth-order derivative of the metrics, so a uniform

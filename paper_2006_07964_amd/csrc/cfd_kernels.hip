@@ -1207,6 +1207,284 @@ template hipError_t launch_sweep_batch<float>(int, int, bool, const SweepBlock*,
                                               hipStream_t);
 
 // =====================================================================================
+// Marching sweep (FP64, eta and zeta, partial sums): one thread per grid line, lanes along i.
+//
+// A thread walks its line of nodes through a chunk of `len` outputs.  At node p it adds the
+// nodal and viscous flux of p to the seven outputs p-3 .. p+3 (kept in registers), evaluates
+// the characteristic WENO pair and split fluxes of node n = p-2, whose stencil p-4 .. p is
+// now complete, and stores output p-4, finished one step earlier.  The last four nodes' Q and
+// metrics sit in LDS slots that only this thread touches, so there is no barrier; the
+// operands of node p+1 are requested before the arithmetic of node p, which takes several
+// memory latencies.
+//
+// Why: the tile kernel is bound by FP64 issue (SIMDs 80-88% busy at the clock the chip holds
+// under this load, about 1.7 GHz) and spends 1036 VALU instructions per point on rows it
+// recomputes (WENO 32/30, nodal fluxes 36/30, half-point metrics twice), projections of
+// states instead of differences and tile addressing; this form takes 740, a quarter of the
+// LDS instructions and reads Q once.  Two waves per SIMD with 230-254 VGPRs: the outputs in
+// flight and the node's basis do not fit less, and the SIMDs are 88-92% busy.
+// Measured, 512 x 512 x 384: zeta 4.47 -> 3.41 ms, eta 4.78 -> 3.71 ms (17.7 GB at 95% of the
+// rate of a device copy); 160^3 193 -> 153 us and 239 -> 168 us.
+// =====================================================================================
+constexpr int kMarchNT = 256;  // threads (grid lines) of a workgroup; two workgroups per CU
+constexpr int kMarchSlot = 8 * kMarchNT;  // LDS doubles of one node: Q (5) and the metric (3)
+
+template <int DIR, bool VIS, bool PREV>
+__device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlock& b, int grp, int chunk, int len,
+                                            double* sh) {
+  static_assert(DIR == 1 || DIR == 2, "lanes run along i");
+  constexpr int NT = kMarchNT;
+  using R = double;
+  const Geom& g = b.g;
+  const int nd = DIR == 1 ? g.nj : g.nk;
+  const int n2 = DIR == 1 ? g.nk : g.nj;
+  const uint32_t sd = DIR == 1 ? (uint32_t)g.ld_i : (uint32_t)(g.ld_i * g.ld_j);
+  const uint32_t s2 = DIR == 1 ? (uint32_t)(g.ld_i * g.ld_j) : (uint32_t)g.ld_i;
+  const int lines = g.ni * n2;
+  const int line = min(grp * NT + (int)threadIdx.x, lines - 1);
+  const bool act = grp * NT + (int)threadIdx.x < lines;  // the others repeat the last line, storing nothing
+  const int o0 = chunk * len, o1 = min(o0 + len, nd);
+  const uint32_t base = (uint32_t)at(g, 0, 0, 0) + (uint32_t)(line % g.ni) + (uint32_t)(line / g.ni) * s2;
+  const Gas<R> G(c.ph);
+  const R eps4 = 4.0 * c.ph.eps;
+
+  GP<const double> Q[5], V[4], I[5], M[3];
+  GP<double> O[5];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    Q[v] = plane_ptr(to_global(b.q), v * g.plane);
+    I[v] = plane_ptr((GP<const double>)to_global(static_cast<const double*>(b.rt_in)), v * g.plane);
+    O[v] = plane_ptr(to_global(static_cast<double*>(b.rt_out)), v * g.plane);
+    if (v < 4) V[v] = plane_ptr((GP<const double>)to_global(static_cast<const double*>(b.vis)), (4 * DIR + v) * g.plane);
+    if (v < 3) M[v] = plane_ptr(to_global(b.met), (3 * DIR + v) * g.plane);
+  }
+
+  struct Operands {
+    R q[5], v[4], m[3];  // Q and viscous flux of node p, metric of node p+1
+  };
+  auto load = [&](Operands& x, int n) {  // indices past the stored planes belong to discarded outputs
+    const uint32_t e = base + (uint32_t)min(n, nd + 2) * sd, em = base + (uint32_t)min(n + 1, nd + 2) * sd;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) x.q[v] = ldg(Q[v], e);
+    if constexpr (VIS) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x.v[v] = ldg(V[v], e);
+    }
+#pragma unroll
+    for (int v = 0; v < 3; ++v) x.m[v] = ldg(M[v], em);
+  };
+
+  // A[o]: right-hand side of output p-3+o so far (two steps per loop round shift it by two)
+  R A[8][5];
+#pragma unroll
+  for (int o = 0; o < 6; ++o)
+#pragma unroll
+    for (int v = 0; v < 5; ++v) A[o][v] = 0.0;
+  R done[5], rr[5];  // output p-4, finished, and its partial sum of the earlier directions
+  auto put = [&](int o) {
+    if (o >= o0 && o < o1 && act) {
+      const uint32_t e = base + (uint32_t)o * sd;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) stg(O[v], e, PREV ? done[v] + rr[v] : done[v]);
+    }
+  };
+  // F+ of the node before at its n+1/2, and the metric of that half point
+  double* const SF = sh + 4 * kMarchSlot + threadIdx.x;
+#pragma unroll
+  for (int v = 0; v < 8; ++v) SF[v * NT] = 1.0;
+  R mag = 1.0, minv = 1.0;
+  R mc[3];  // metric of node p
+
+  // one node; S0 .. S3 are the slots of nodes p-4 .. p-1, and S0 takes node p
+  auto step = [&](int p, R(*A)[5], const Operands& x, Operands& next, double* S0, const double* S1, const double* S2,
+                  const double* S3) {
+    load(next, p + 1);
+    __builtin_amdgcn_sched_barrier(0);  // phase borders: the scheduler would overlap phases into spills
+    R F[5];
+    phys_flux(x.q, mc[0], mc[1], mc[2], G, F);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {  // Eq 19
+      A[0][v] -= R(19.0 / 3840.0) * F[v];
+      A[1][v] += R(13.0 / 320.0) * F[v];
+      A[2][v] -= R(17.0 / 256.0) * F[v];
+      A[4][v] += R(17.0 / 256.0) * F[v];
+      A[5][v] -= R(13.0 / 320.0) * F[v];
+      A[6][v] = R(19.0 / 3840.0) * F[v];
+    }
+    if constexpr (VIS) {
+#pragma unroll
+      for (int v = 1; v < 5; ++v) {  // d6 of the viscous flux
+        A[0][v] += R(1.0 / 60.0) * x.v[v - 1];
+        A[1][v] -= R(0.15) * x.v[v - 1];
+        A[2][v] += R(0.75) * x.v[v - 1];
+        A[4][v] -= R(0.75) * x.v[v - 1];
+        A[5][v] += R(0.15) * x.v[v - 1];
+        A[6][v] -= R(1.0 / 60.0) * x.v[v - 1];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    put(p - 4);
+    if (p > o0) {  // node n = p-2, from n = o0-1 on
+      R qn[5], mn[3], h[3];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) qn[v] = S2[v * NT];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) {  // half_metric at n+1/2
+        mn[v] = S2[(5 + v) * NT];
+        h[v] = R(3.0 / 256.0) * (S0[(5 + v) * NT] + x.m[v]) - R(25.0 / 256.0) * (S1[(5 + v) * NT] + mc[v]) +
+               R(150.0 / 256.0) * (mn[v] + S3[(5 + v) * NT]);
+      }
+      const NodeSpace<R> B = node_space(qn, mn[0], mn[1], mn[2], G);
+      R D[4][5];  // projected first differences of Q along p-4 .. p
+      {
+        R a[5], d[5], t[5];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) a[v] = S1[v * NT], t[v] = a[v] - S0[v * NT];
+        project_diff(B, t, D[0]);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) t[v] = qn[v] - a[v];
+        project_diff(B, t, D[1]);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) d[v] = S3[v * NT], t[v] = d[v] - qn[v];
+        project_diff(B, t, D[2]);
+#pragma unroll
+        for (int v = 0; v < 5; ++v) t[v] = x.q[v] - d[v], S0[v * NT] = x.q[v];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) S0[(5 + v) * NT] = mc[v];
+        project_diff(B, t, D[3]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      R vl[5], vr[5];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        weno_diff<R>(D[0][f], D[1][f], D[2][f], D[3][f], eps4, vl[f], vr[f]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (PREV) {  // requested here, past the peak of register use, for the next step's put
+        const uint32_t e = base + (uint32_t)max(p - 3, 0) * sd;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) rr[v] = ldg(I[v], e);
+      }
+      half_flux<-1>(B, G, vr, SF[5 * NT], SF[6 * NT], SF[7 * NT], mag, minv, F);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        const R f = SF[v * NT] + F[v];  // f(n-1/2) = F+(n-1) + F-(n)
+        A[0][v] -= f;
+        A[1][v] += f;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const R m2 = h[0] * h[0] + h[1] * h[1] + h[2] * h[2];
+      minv = rsq(m2);
+      mag = m2 * minv;
+      half_flux<+1>(B, G, vl, h[0], h[1], h[2], mag, minv, F);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) SF[v * NT] = F[v];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) SF[(5 + v) * NT] = h[v];
+    } else {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) S0[v * NT] = x.q[v];
+#pragma unroll
+      for (int v = 0; v < 3; ++v) S0[(5 + v) * NT] = mc[v];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) done[v] = A[0][v];
+#pragma unroll
+    for (int v = 0; v < 3; ++v) mc[v] = x.m[v];
+  };
+
+  double* S[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) S[n] = sh + n * kMarchSlot + threadIdx.x;
+  int p = o0 - 3;
+#pragma unroll
+  for (int v = 0; v < 3; ++v) mc[v] = ldg(M[v], base + (uint32_t)p * sd);
+  Operands even, odd;
+  load(even, p);
+  // output o is final after step o+3; the last step may be one past the chunk
+#pragma unroll 1
+  for (; p < o1 + 3; p += 2) {
+    step(p, A, even, odd, S[0], S[1], S[2], S[3]);
+    step(p + 1, A + 1, odd, even, S[1], S[2], S[3], S[0]);
+    double* t = S[0];
+    S[0] = S[2];
+    S[2] = t;
+    t = S[1];
+    S[1] = S[3];
+    S[3] = t;
+#pragma unroll
+    for (int o = 0; o < 6; ++o)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) A[o][v] = A[o + 2][v];
+  }
+  if (p == o1 + 3) put(o1 - 1);  // no step past the chunk stored it
+}
+
+template <int DIR, bool VIS, bool PREV>
+__global__ __launch_bounds__(kMarchNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_march(SweepArgs a, int groups,
+                                                                                              int len) {
+  __shared__ double sh[5 * kMarchSlot];
+  const int t = xcd_remap(blockIdx.x, gridDim.x);
+  march_lines<DIR, VIS, PREV>(a.c, a.b, t % groups, t / groups, len, sh);
+}
+
+// Chunk length of the marching sweep, or 0 where the tiles are faster.  A workgroup puts one
+// wave on each SIMD of its CU, two keep the SIMDs busy, and a step of a wave takes one unit
+// (2.45 us in eta with a partial sum, 2.2 us in zeta without) of SIMD time; a chunk of len
+// outputs costs len + 2.6 steps (two more WENO nodes, four nodes without), and a launch takes
+// the time of the CU with most workgroups, 15% more where that is one workgroup, whose
+// latencies nothing fills.  The tiles take 46-58 ps per point (eta) and 44-53 (zeta), i.e. a
+// unit per 47000 points.  Measured eta, tiles / march: 96x80x72 31 / 32 us (tiles kept),
+// 160x88x96 64 / 61, 144x120x100 83 / 79, 192x112x72 74 / 69, 128^3 110 / 89, 190x131x93
+// 125 / 103, 256^3 890 / 641.
+static int march_len(int dir, const Geom& g) {
+  const int nd = dir == 1 ? g.nj : g.nk, n2 = dir == 1 ? g.nk : g.nj;
+  const int64_t groups = ((int64_t)g.ni * n2 + kMarchNT - 1) / kMarchNT;
+  const double points = (double)g.ni * g.nj * g.nk;
+  double best = points / 47000.0;
+  int best_len = 0;
+  for (int chunks = 1; chunks <= nd; ++chunks) {
+    const int len = (nd + chunks - 1) / chunks;
+    const int64_t wgs = groups * ((nd + len - 1) / len);
+    if (wgs > 16 * 1024 && chunks > 1) break;  // many rounds already
+    const int64_t rounds = (wgs + 255) / 256;
+    const double cost = (rounds == 1 ? 1.15 : (double)rounds) * (len + 2.6);
+    if (cost < best) best = cost, best_len = len;
+  }
+  return best_len;
+}
+
+template <int DIR>
+static void launch_march_dir(const SweepArgs& a, int groups, int chunks, int len, hipStream_t s) {
+  const dim3 grid(groups * chunks), wg(kMarchNT);
+  if (a.c.do_vis && a.c.has_prev)
+    hipLaunchKernelGGL((k_march<DIR, true, true>), grid, wg, 0, s, a, groups, len);
+  else if (a.c.do_vis)
+    hipLaunchKernelGGL((k_march<DIR, true, false>), grid, wg, 0, s, a, groups, len);
+  else if (a.c.has_prev)
+    hipLaunchKernelGGL((k_march<DIR, false, true>), grid, wg, 0, s, a, groups, len);
+  else
+    hipLaunchKernelGGL((k_march<DIR, false, false>), grid, wg, 0, s, a, groups, len);
+}
+
+bool launch_march(int dir, const SweepArgs& a, hipStream_t s, hipError_t* err) {
+  const bool os = (a.b.one_sided >> (2 * dir)) & 3;
+  if (dir == 0 || a.c.out_kind != kOutPartial || !a.c.do_inv || a.c.ph.linear || a.c.ph.scheme != kModified || os)
+    return false;
+  const int len = march_len(dir, a.b.g);
+  if (!len) return false;
+  const int nd = dir == 1 ? a.b.g.nj : a.b.g.nk, n2 = dir == 1 ? a.b.g.nk : a.b.g.nj;
+  const int groups = (int)(((int64_t)a.b.g.ni * n2 + kMarchNT - 1) / kMarchNT), chunks = (nd + len - 1) / len;
+  if (dir == 1)
+    launch_march_dir<1>(a, groups, chunks, len, s);
+  else
+    launch_march_dir<2>(a, groups, chunks, len, s);
+  *err = hipGetLastError();
+  return true;
+}
+
+// =====================================================================================
 // Halo copies across 1-to-1 faces (ghost layer m of the destination face <- interior
 // layer m-1 inside the source face), boundary fills.
 // =====================================================================================

@@ -110,6 +110,10 @@ int sweep_threads(int cfg);
 template <typename R>
 hipError_t launch_sweep(int dir, SweepArgs a, hipStream_t s, int cfg = 0);
 
+// FP64 eta or zeta sweep into partial sums by lines (JS weights, modified scheme, no one-sided
+// closure along dir), where it is faster than the tiles; false: nothing launched
+bool launch_march(int dir, const SweepArgs& a, hipStream_t s, hipError_t* err);
+
 template <typename R>
 hipError_t launch_sweep_batch(int dir, int cfg, bool persist, const SweepBlock* blocks_dev, const SweepCommon& c,
                               const TileList& tl, int nwg, hipStream_t s);
