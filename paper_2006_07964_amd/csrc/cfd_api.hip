@@ -505,6 +505,8 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     hipError_t e = hipSuccess;
     if (b->d.precision != CFD_FP64)
       e = launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
+    else if (!b->own_tiles && dirs[n] == 0 && inv && a.c.ph.scheme == CFD_AFWENO_MODIFIED)
+      e = launch_sweep_rows(a, b->stream);
     else if (b->own_tiles || !launch_march(dirs[n], a, b->stream, &e))
       e = launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
     ps.done();
@@ -1117,7 +1119,8 @@ void build_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* con
     double* const* cur = st == 0 ? Qn : st == 1 ? QA : QB;
     double* const* outp = st == 0 ? QA : st == 1 ? QB : Qn;
     for (int n = 0; n < 3; ++n) {
-      SweepCommon& c = bt->sweep_common[st][kSweepOrder[n]];
+      const int d = kSweepOrder[n];
+      SweepCommon& c = bt->sweep_common[st][d];
       std::memset(&c, 0, sizeof c);
       c.ph = ph;
       c.do_inv = 1;
@@ -1125,7 +1128,7 @@ void build_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* con
       c.has_prev = n > 0;
       c.out_kind = n == 2 ? kOutRK : kOutPartial;
       c.dt_dev = dt_dev;
-      c.one_sided = bt->one_sided;
+      for (const cfd_block* B : bt->blocks) c.one_sided |= (one_sided_mask(B->d) >> (2 * d)) & 3;
       c.ca = kRK[st][0];
       c.cb = kRK[st][1];
       c.cc = kRK[st][2];

@@ -436,12 +436,17 @@ __device__ __forceinline__ void project_diff(const NodeSpace<R>& B, const R x[5]
 // weno_pair's correction form from the first differences D1..D4 of the five values: eight
 // times the values at i+1/2 (cl) and i-1/2 (cr) minus the centre value; eps4 = 4 eps
 template <typename R>
-__device__ __forceinline__ void weno_diff(R D1, R D2, R D3, R D4, R eps4, R& cl, R& cr) {
+__device__ __forceinline__ void weno_diff(R D1, R D2, R D3, R D4, R eps4, bool linear, R& cl, R& cr) {
   const R d0 = D2 - D1, e0 = R(3) * D2 - D1;
   const R d1 = D3 - D2, e1 = -(D2 + D3);
   const R d2 = D4 - D3, e2 = D4 - R(3) * D3;
   const R A0 = d0 + R(2) * e0, A1 = d1 - R(2) * e1, A2 = d2 - R(2) * e2;
   const R B0 = d0 - R(2) * e0, B1 = d1 + R(2) * e1, B2 = d2 + R(2) * e2;
+  if (linear) {  // ideal weights (1, 10, 5)/16 at i+1/2 and (5, 10, 1)/16 at i-1/2
+    cl = (A0 + R(10) * A1 + R(5) * A2) * R(1.0 / 16.0);
+    cr = (R(5) * B0 + R(10) * B1 + B2) * R(1.0 / 16.0);
+    return;
+  }
   const R t0 = R(13.0 / 3.0) * d0 * d0 + (e0 * e0 + eps4);
   const R t1 = R(13.0 / 3.0) * d1 * d1 + (e1 * e1 + eps4);
   const R t2 = R(13.0 / 3.0) * d2 * d2 + (e2 * e2 + eps4);
@@ -496,7 +501,7 @@ __device__ __forceinline__ void half_flux(const NodeSpace<R>& B, const Gas<R>& G
 // state stays uniform on curvilinear grids.  g(m) returns the node value at offset m.
 template <typename F>
 __device__ __forceinline__ double half_metric(F g) {
-  return (3.0 * (g(-2) + g(3)) - 25.0 * (g(-1) + g(2)) + 150.0 * (g(0) + g(1))) * (1.0 / 256.0);
+  return (3.0 / 256.0) * (g(-2) + g(3)) - (25.0 / 256.0) * (g(-1) + g(2)) + (150.0 / 256.0) * (g(0) + g(1));
 }
 
 }  // namespace cfd

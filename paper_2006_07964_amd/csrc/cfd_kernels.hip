@@ -571,6 +571,25 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
   constexpr int NN = SweepLds<TW, TS>::NN;
   constexpr int NW = SweepLds<TW, TS>::NW;
   using L = LdsIdx<DIR, TW>;
+  // xi tiles with 64 threads per line: a wave owns a line, reads no other wave's LDS and so
+  // needs no barrier, only the order of its own LDS accesses; the waves of a workgroup drift
+  // apart, which overlaps one's staging with another's arithmetic
+  constexpr bool WAVE_LINE = DIR == 0 && NT == 64 * TW && NW <= 64;
+  constexpr int SPAN = WAVE_LINE ? 64 : NT;  // threads that share the items of a phase
+  // item e of a phase with len entries per line: its line and entry
+  auto line_of = [](int e, int len) { return WAVE_LINE ? (int)(threadIdx.x >> 6) : DIR == 0 ? e / len : e % TW; };
+  auto node_of = [](int e, int len) { return WAVE_LINE ? e : DIR == 0 ? e % len : e / TW; };
+  constexpr int LINES = WAVE_LINE ? 1 : TW;  // lines behind the items of a phase
+  const int tid = WAVE_LINE ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+  auto tile_sync = []() {
+    if constexpr (WAVE_LINE) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
 
   const Geom& g = b.g;
   const int nd = DIR == 0 ? g.ni : DIR == 1 ? g.nj : g.nk;
@@ -608,13 +627,11 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
 
   // ---- the output node of this thread (at most one per thread) and its global operands,
   // requested before the last barrier so that their latency overlaps the nodal-flux phase
-  static_assert(TW * TS <= NT, "one output node per thread");
+  static_assert(LINES * TS <= SPAN, "one output node per thread");
   const GP<const R> vis = to_global(static_cast<const R*>(b.vis)) + (4 * DIR) * plane;
   const GP<const R> rin = to_global(static_cast<const R*>(b.rt_in));
-  const int eo = threadIdx.x;
-  const int so = DIR == 0 ? eo % TS : eo / TW;
-  const int wo = DIR == 0 ? eo / TS : eo % TW;
-  const bool out_here = eo < TW * TS && so < ts && c1_0 + wo < n1 && d0 + so < nd;
+  const int so = node_of(tid, TS), wo = line_of(tid, TS);
+  const bool out_here = tid < LINES * TS && so < ts && c1_0 + wo < n1 && d0 + so < nd;
   const uint32_t po = origin + (uint32_t)(c1_0 + wo) * s1 + (uint32_t)(d0 + so) * sd;
   R vm[4][6];  // viscous fluxes of the direction at offsets -3, -2, -1, 1, 2, 3
   R rp[5];     // partial sums of the earlier directions
@@ -660,19 +677,18 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
     // A thread's items (at most ITEMS) have all their loads issued before the first LDS
     // store, so the tile waits for one memory round trip rather than one per item.
     {
-      constexpr int ITEMS = (TW * NN + NT - 1) / NT;
+      constexpr int ITEMS = (LINES * NN + SPAN - 1) / SPAN;
       double ld[ITEMS][12];  // Q, then (FP64) node metrics and viscous fluxes
       R lr[ITEMS][10];       // mixed precision: node metrics, viscous fluxes, half-point metrics
       bool ok[ITEMS], okh[ITEMS];
       int li[ITEMS], lhi[ITEMS];
 #pragma unroll
       for (int it = 0; it < ITEMS; ++it) {
-        const int e = threadIdx.x + it * NT;
-        const int s = DIR == 0 ? e % NN : e / TW;
-        const int w = DIR == 0 ? e / NN : e % TW;
+        const int e = tid + it * SPAN;
+        const int s = node_of(e, NN), w = line_of(e, NN);
         const int n = d0 - 3 + s;
         const int c1 = c1_0 + w;
-        ok[it] = e < TW * NN && s < nn && c1 < n1 && n <= nd + 2;
+        ok[it] = e < LINES * NN && s < nn && c1 < n1 && n <= nd + 2;
         li[it] = L::f(0, w, s, NN);
         if (ok[it]) {
           const uint32_t p = origin + (uint32_t)c1 * s1 + (uint32_t)n * sd;
@@ -731,7 +747,7 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
         }
       }
     }
-    __syncthreads();
+    tile_sync();
     R Fkeep[5];
     bool need_m = false;
     int ww = 0, sw_ = 0;
@@ -739,11 +755,10 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
       // ---- characteristic WENO pair and split fluxes (one node per thread); node n = d0-1+s
       // sits at staged index s+2.  F+ at n+1/2 goes to LDS now; F- at n-1/2 is added to the
       // same interface after the barrier, so sF holds f(n+1/2) = F+(n) + F-(n+1). ----------
-      static_assert(TW * NW <= NT, "one WENO node per thread");
-      const int ew = threadIdx.x;
-      sw_ = DIR == 0 ? ew % NW : ew / TW;
-      ww = DIR == 0 ? ew / NW : ew % TW;
-      const bool wvalid = ew < TW * NW && sw_ < nw && c1_0 + ww < n1 && d0 - 1 + sw_ <= nd;
+      static_assert(LINES * NW <= SPAN, "one WENO node per thread");
+      sw_ = node_of(tid, NW);
+      ww = line_of(tid, NW);
+      const bool wvalid = tid < LINES * NW && sw_ < nw && c1_0 + ww < n1 && d0 - 1 + sw_ <= nd;
       const bool need_p = wvalid && sw_ <= ts && d0 - 1 + sw_ <= nd - 1;  // F+ at n+1/2
       need_m = wvalid && sw_ >= 1;                                        // F- at n-1/2
       if (need_p || need_m) {
@@ -752,24 +767,21 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
         R q0[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) q0[v] = R(sFn[L::f(v, w, sc, NN)]);
-        const Basis<R> B =
-            make_basis(q0, R(sM[L::f(0, w, sc, NN)]), R(sM[L::f(1, w, sc, NN)]), R(sM[L::f(2, w, sc, NN)]), G);
-        R V[5][5];  // V[t][field] at node n + t - 2
-#pragma unroll
-        for (int tt = 0; tt < 5; ++tt) {
-          R qq[5];
-#pragma unroll
-          for (int v = 0; v < 5; ++v) qq[v] = R(sFn[L::f(v, w, s + tt, NN)]);
-          project(B, G, qq, V[tt]);
-        }
-        R vl[5], vr[5];
-        // FP64: the correction form (2.4% and 1.5% faster zeta and eta sweeps), except in the
-        // RK sweep, whose registers it would overflow (2 VGPRs spilled, 4% slower)
-        constexpr bool kCorr = sizeof(R) == 8 && DIR != kSweepOrder[2];
-#pragma unroll
-        for (int f = 0; f < 5; ++f)
-          weno_pair<R, kCorr>(V[0][f], V[1][f], V[2][f], V[3][f], V[4][f], eps, linear, vl[f], vr[f]);
+        const R m0 = R(sM[L::f(0, w, sc, NN)]), m1 = R(sM[L::f(1, w, sc, NN)]), m2 = R(sM[L::f(2, w, sc, NN)]);
         if constexpr (kHalfPre<R>) {
+          const Basis<R> B = make_basis(q0, m0, m1, m2, G);
+          R V[5][5];  // V[t][field] at node n + t - 2
+#pragma unroll
+          for (int tt = 0; tt < 5; ++tt) {
+            R qq[5];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) qq[v] = R(sFn[L::f(v, w, s + tt, NN)]);
+            project(B, G, qq, V[tt]);
+          }
+          R vl[5], vr[5];
+#pragma unroll
+          for (int f = 0; f < 5; ++f)
+            weno_pair<R>(V[0][f], V[1][f], V[2][f], V[3][f], V[4][f], eps, linear, vl[f], vr[f]);
           // half-point metrics from LDS: slot s holds n+1/2, slot s-1 holds n-1/2
           if (need_p) {
             R ul[5], F[5];
@@ -786,25 +798,39 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
             sw_flux<-1>(ur, hx, hy, hz, G, Fkeep);
           }
         } else {
-          // half-point metrics interpolated from the staged node metrics
+          const NodeSpace<R> B = node_space(q0, m0, m1, m2, G);
+          R D[4][5];  // projected first differences of Q along n-2 .. n+2
+#pragma unroll
+          for (int tt = 0; tt < 4; ++tt) {
+            R t[5];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) t[v] = sFn[L::f(v, w, s + tt + 1, NN)] - sFn[L::f(v, w, s + tt, NN)];
+            project_diff(B, t, D[tt]);
+          }
+          R vl[5], vr[5];
+          const R eps4 = R(4) * eps;
+#pragma unroll
+          for (int f = 0; f < 5; ++f) weno_diff<R>(D[0][f], D[1][f], D[2][f], D[3][f], eps4, linear, vl[f], vr[f]);
+          // half-point metrics interpolated from the staged node metrics; the half point n-1/2
+          // = (n-1)+1/2 is centred on staged index sc-1
+          auto half = [&](int at, R h[3], R& mag, R& minv) {
+#pragma unroll
+            for (int d = 0; d < 3; ++d) h[d] = half_metric([&](int m) { return sM[L::f(d, w, at + m, NN)]; });
+            const R hh = h[0] * h[0] + h[1] * h[1] + h[2] * h[2];
+            minv = rsq(hh);
+            mag = hh * minv;
+          };
+          R h[3], mag, minv;
           if (need_p) {
-            R ul[5], F[5];
-            unproject(B, G, vl, ul);
-            const R hx = R(half_metric([&](int m) { return sM[L::f(0, w, sc + m, NN)]; }));
-            const R hy = R(half_metric([&](int m) { return sM[L::f(1, w, sc + m, NN)]; }));
-            const R hz = R(half_metric([&](int m) { return sM[L::f(2, w, sc + m, NN)]; }));
-            sw_flux<+1>(ul, hx, hy, hz, G, F);
+            R F[5];
+            half(sc, h, mag, minv);
+            half_flux<+1>(B, G, vl, h[0], h[1], h[2], mag, minv, F);
 #pragma unroll
             for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] = F[v];
           }
           if (need_m) {
-            R ur[5];
-            unproject(B, G, vr, ur);
-            // half point n-1/2 = (n-1)+1/2, centred on staged index sc-1
-            const R hx = R(half_metric([&](int m) { return sM[L::f(0, w, sc - 1 + m, NN)]; }));
-            const R hy = R(half_metric([&](int m) { return sM[L::f(1, w, sc - 1 + m, NN)]; }));
-            const R hz = R(half_metric([&](int m) { return sM[L::f(2, w, sc - 1 + m, NN)]; }));
-            sw_flux<-1>(ur, hx, hy, hz, G, Fkeep);
+            half(sc - 1, h, mag, minv);
+            half_flux<-1>(B, G, vr, h[0], h[1], h[2], mag, minv, Fkeep);
           }
         }
       }
@@ -814,11 +840,9 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
       // characteristic space sits at the half point: the mean state of n and n+1 and the
       // direction of the half-point metric; the value left of n+1/2 comes from nodes
       // n-2..n+2, the value right of it from n-1..n+3, and f(n+1/2) = F+ + F- directly.
-      static_assert(TW * NH <= NT, "one half point per thread");
-      const int eh = threadIdx.x;
-      const int s = DIR == 0 ? eh % NH : eh / TW;
-      const int w = DIR == 0 ? eh / NH : eh % TW;
-      if (eh < TW * NH && s <= ts && c1_0 + w < n1 && d0 - 1 + s <= nd - 1) {
+      static_assert(LINES * NH <= SPAN, "one half point per thread");
+      const int s = node_of(tid, NH), w = line_of(tid, NH);
+      if (tid < LINES * NH && s <= ts && c1_0 + w < n1 && d0 - 1 + s <= nd - 1) {
         const int sc = s + 2;
         // half-point metric: read from LDS in mixed precision; in FP64 formed again where it
         // is used rather than held in registers
@@ -867,16 +891,15 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
 #pragma unroll
       for (int v = 0; v < 5; ++v) qco[v] = double(sFn[L::f(v, wo, so + 3, NN)]);
     }
-    __syncthreads();
+    tile_sync();
     if (need_m) {  // each interface receives exactly one F-
 #pragma unroll
       for (int v = 0; v < 5; ++v) sF[L::f(v, ww, sw_ - 1, NH)] += Fkeep[v];
     }
     fetch();
     // ---- nodal fluxes, Eq 4, in place of the staged Q ------------------------------------
-    for (int e = threadIdx.x; e < TW * NN; e += NT) {
-      const int s = DIR == 0 ? e % NN : e / TW;
-      const int w = DIR == 0 ? e / NN : e % TW;
+    for (int e = tid; e < LINES * NN; e += SPAN) {
+      const int s = node_of(e, NN), w = line_of(e, NN);
       const int n = d0 - 3 + s;
       const int c1 = c1_0 + w;
       if (s >= nn || c1 >= n1 || n > nd + 2) continue;
@@ -887,7 +910,7 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
 #pragma unroll
       for (int v = 0; v < 5; ++v) sFn[L::f(v, w, s, NN)] = F[v];
     }
-    __syncthreads();
+    tile_sync();
   }
 
   // ---- assembly at the output node ------------------------------------------------------
@@ -912,15 +935,28 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
     int first = 0, row = 0, sign = 0;
     if (OS && one_sided_window((b.one_sided >> (2 * DIR)) & 3, d0 + s, nd, &first, &row, &sign)) {
       // a node next to a one-sided face: seven-point one-sided derivative over the nodes
-      // nearest the face, read from memory (the tile need not hold them)
+      // nearest the face, from the staged tile where it holds them (all but a last tile of
+      // fewer than four nodes), else from memory
+      R acc[4] = {R(0), R(0), R(0), R(0)};
+      const int at0 = first - (d0 - 3);  // staged index of the window
+      if (c.do_inv && at0 >= 0 && at0 + 6 < nn) {
 #pragma unroll 1
-      for (int v = 1; v < 5; ++v) {
-        const GP<const R> vp = plane_ptr(vis, (v - 1) * plane);
-        R acc = R(0);
+        for (int m = 0; m < 7; ++m) {
+          const R wgt = R(os6_weight(row, sign, m));
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[v] += wgt * sV[L::f(v, w, at0 + m, NN)];
+        }
+      } else {
 #pragma unroll 1
-        for (int m = 0; m < 7; ++m) acc += R(os6_weight(row, sign, m)) * ldg(vp, po + (uint32_t)(first + m - d0 - s) * sd);
-        r[v] += acc;
+        for (int m = 0; m < 7; ++m) {
+          const R wgt = R(os6_weight(row, sign, m));
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            acc[v] += wgt * ldg(plane_ptr(vis, v * plane), po + (uint32_t)(first + m - d0 - s) * sd);
+        }
       }
+#pragma unroll
+      for (int v = 1; v < 5; ++v) r[v] += acc[v - 1];
     } else if (c.do_inv) {
 #pragma unroll
       for (int v = 1; v < 5; ++v) r[v] += d6<R>([&](int m) { return sV[L::f(v - 1, w, s + 3 + m, NN)]; });
@@ -1108,12 +1144,33 @@ hipError_t launch_sweep_scheme(int dir, const SweepArgs& a, int64_t nwg, hipStre
 
 template <typename R, int CFG>
 hipError_t launch_sweep_cfg(int dir, const SweepArgs& a, int64_t nwg, hipStream_t s) {
-  const bool os = a.b.one_sided != 0;
+  const bool os = (a.b.one_sided >> (2 * dir)) & 3;  // the closure acts on faces across the sweep
   if (a.c.ph.scheme == kOriginal)
     return os ? launch_sweep_scheme<R, CFG, kOriginal, true>(dir, a, nwg, s)
               : launch_sweep_scheme<R, CFG, kOriginal, false>(dir, a, nwg, s);
   return os ? launch_sweep_scheme<R, CFG, kModified, true>(dir, a, nwg, s)
             : launch_sweep_scheme<R, CFG, kModified, false>(dir, a, nwg, s);
+}
+
+// FP64 xi sweep with a workgroup of one wave per line of up to 58 nodes: the wave-per-line tile
+// (4 x 58) without three neighbours whose LDS and registers wait for the slowest of the four.
+// xi + RK sweep, 4 x 58 / one line: 128^3 122 / 117 us, 160^3 218 / 201, 256^3 862 / 835,
+// 512 x 512 x 384 4.95 / 4.83 ms (5.28 before waves owned lines).
+constexpr int kRowNodes = 58;
+
+hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s) {
+  const Geom& g = a.b.g;
+  a.b.tiles_c1 = g.nj;
+  a.b.tiles_d = (g.ni + kRowNodes - 1) / kRowNodes;
+  a.b.tile_len = (g.ni + a.b.tiles_d - 1) / a.b.tiles_d;
+  const int64_t nwg = (int64_t)a.b.tiles_c1 * a.b.tiles_d * g.nk;
+  if (nwg > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)nwg), wg(64);
+  if (a.b.one_sided & 3)
+    hipLaunchKernelGGL((k_sweep<0, double, 1, kRowNodes, 64, kModified, true>), grid, wg, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_sweep<0, double, 1, kRowNodes, 64, kModified, false>), grid, wg, 0, s, a);
+  return hipGetLastError();
 }
 
 template <typename R>
@@ -1357,7 +1414,7 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
       R vl[5], vr[5];
 #pragma unroll
       for (int f = 0; f < 5; ++f) {
-        weno_diff<R>(D[0][f], D[1][f], D[2][f], D[3][f], eps4, vl[f], vr[f]);
+        weno_diff<R>(D[0][f], D[1][f], D[2][f], D[3][f], eps4, false, vl[f], vr[f]);
         __builtin_amdgcn_sched_barrier(0);
       }
       if constexpr (PREV) {  // requested here, past the peak of register use, for the next step's put

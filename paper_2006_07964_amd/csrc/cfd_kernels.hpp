@@ -91,7 +91,7 @@ struct SweepCommon {
   Phys ph;
   int do_inv, do_vis, has_prev, out_kind;
   int one_sided;  // some block of the launch has faces with the one-sided viscous closure
-                  // (selects the kernels that evaluate it; batched launches only)
+                  // across the sweep (selects the kernels that evaluate it; batched only)
 };
 struct SweepArgs {
   SweepCommon c;
@@ -109,6 +109,9 @@ void sweep_tiling(int dir, int cfg, const Geom& g, int* tiles_c1, int* tiles_d, 
 int sweep_threads(int cfg);
 template <typename R>
 hipError_t launch_sweep(int dir, SweepArgs a, hipStream_t s, int cfg = 0);
+
+// FP64 xi sweep of the modified scheme, one wave per line
+hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s);
 
 // FP64 eta or zeta sweep into partial sums by lines (JS weights, modified scheme, no one-sided
 // closure along dir), where it is faster than the tiles; false: nothing launched
