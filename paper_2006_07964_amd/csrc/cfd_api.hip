@@ -152,9 +152,11 @@ struct cfd_block {
   bool own_tiles = false;  // the caller chose the shapes: every sweep runs them
   // small device scratch for reductions
   unsigned long long* red_dev = nullptr;
+  bool red_dirty = true;  // red_dev is not known to be cleared
   int* flag_dev = nullptr;
   double* res_dev = nullptr;  // residual partial rows of up to kMaxBlocks blocks (allocated on first use)
   const double* dt_field = nullptr;  // caller's per-point time steps (local time stepping) or null
+  double* pin = nullptr;  // pinned host memory the reductions write their results to (allocated on first use)
   hipEvent_t ev = nullptr;    // orders this block's stream before another block's
   Profiler prof;
 };
@@ -528,6 +530,18 @@ int check_rk_args(cfd_block* b, int stage, const double* Qn, const double* Qcur,
   return CFD_OK;
 }
 
+// Pinned host memory of a block's synchronising reductions: the last kernel writes its few
+// numbers there, which the wait that follows makes visible (a copy from device memory costs
+// another 8 us).
+int pinned_results(cfd_block* b) {
+  if (b->pin) return CFD_OK;
+  if (hipHostMalloc((void**)&b->pin, 16 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    b->pin = nullptr;
+    return fail(CFD_ERR_ALLOC, "pinned result memory");
+  }
+  return CFD_OK;
+}
+
 // Residual scratch of cfd_residual_noalloc: kResGroups partial rows of up to kMaxBlocks
 // blocks and the 10 results, in a file-scope device array (1.31 MB per device, held until
 // the process ends).  Host code never uses the array's name as an address: the device
@@ -632,6 +646,7 @@ int cfd_block_destroy(cfd_block* b) {
   (void)hipFree(b->red_dev);
   (void)hipFree(b->flag_dev);
   (void)hipFree(b->res_dev);
+  if (b->pin) (void)hipHostFree(b->pin);
   if (b->ev) (void)hipEventDestroy(b->ev);
   (void)hipFree(b->local_copy_dev);
   (void)hipFree(b->local_bc_dev);
@@ -762,13 +777,30 @@ int cfd_sync(cfd_block* b) {
 
 int cfd_check_finite(cfd_block* b, const double* Q, int* ok) {
   if (!b || !Q || !ok) return fail(CFD_ERR_ARG, "null argument");
-  int flag = 0;
-  HIP_TRY(hipMemsetAsync(b->flag_dev, 0, sizeof(int), b->stream), "memset");
-  HIP_TRY(launch_finite(b->g, Q, b->flag_dev, b->stream), "finite check launch");
-  HIP_TRY(hipMemcpyAsync(&flag, b->flag_dev, sizeof(int), hipMemcpyDeviceToHost, b->stream), "copy flag");
+  int rc = pinned_results(b);
+  if (rc != CFD_OK) return rc;
+  volatile int* flag = reinterpret_cast<volatile int*>(b->pin);
+  *flag = 0;
+  HIP_TRY(launch_finite(b->g, Q, reinterpret_cast<int*>(b->pin), b->stream), "finite check launch");
   HIP_TRY(hipStreamSynchronize(b->stream), "stream synchronize");
-  *ok = flag ? 0 : 1;
-  return flag ? fail(CFD_ERR_NONFINITE, "non-finite value in state") : CFD_OK;
+  *ok = *flag ? 0 : 1;
+  return *ok ? CFD_OK : fail(CFD_ERR_NONFINITE, "non-finite value in state");
+}
+
+// The step of all blocks on the first block's stream, written to *dt (device or pinned
+// memory).  The accumulator is cleared by the launch that reads it, so it needs clearing only
+// before its first use and after a call that failed between launches.
+static int dt_launches(cfd_block* const* blocks, int nb, const double* const* Q, double cfl, double* dt) {
+  cfd_block* b0 = blocks[0];
+  if (b0->red_dirty) HIP_TRY(launch_dt_reset(b0->red_dev, b0->stream), "dt reset launch");
+  b0->red_dirty = true;
+  for (int n = 0; n < nb; ++n) {
+    cfd_block* b = blocks[n];
+    HIP_TRY(launch_dt_max(b->g, Q[n], b->met, b->d.params.gamma, b0->red_dev, b0->stream), "dt launch");
+  }
+  HIP_TRY(launch_dt_finish(b0->red_dev, cfl, dt, b0->stream), "dt finish launch");
+  b0->red_dirty = false;
+  return CFD_OK;
 }
 
 int cfd_dt_cfl(cfd_block* const* blocks, int nb, const double* const* Q, double cfl, double* dt_out) {
@@ -783,18 +815,13 @@ int cfd_dt_cfl(cfd_block* const* blocks, int nb, const double* const* Q, double 
   // the reduction runs on the first block's stream: finish earlier work of the others
   for (int n = 1; n < nb; ++n)
     if (blocks[n]->stream != b0->stream) HIP_TRY(hipStreamSynchronize(blocks[n]->stream), "stream synchronize");
-  HIP_TRY(hipMemsetAsync(b0->red_dev, 0, sizeof(unsigned long long), b0->stream), "memset");
-  for (int n = 0; n < nb; ++n) {
-    cfd_block* b = blocks[n];
-    HIP_TRY(launch_dt_max(b->g, Q[n], b->met, b->d.params.gamma, b0->red_dev, b0->stream), "dt launch");
-  }
-  unsigned long long bits = 0;
-  HIP_TRY(hipMemcpyAsync(&bits, b0->red_dev, sizeof bits, hipMemcpyDeviceToHost, b0->stream), "copy dt");
+  int rc = pinned_results(b0);
+  if (rc == CFD_OK) rc = dt_launches(blocks, nb, Q, cfl, b0->pin);
+  if (rc != CFD_OK) return rc;
   HIP_TRY(hipStreamSynchronize(b0->stream), "stream synchronize");
-  double smax;
-  std::memcpy(&smax, &bits, sizeof smax);
-  if (!(smax > 0.0) || !std::isfinite(smax)) return fail(CFD_ERR_NONFINITE, "spectral radius is not positive and finite");
-  *dt_out = cfl / smax;
+  const double dt = *static_cast<volatile double*>(b0->pin);
+  if (std::isnan(dt)) return fail(CFD_ERR_NONFINITE, "spectral radius is not positive and finite");
+  *dt_out = dt;
   return CFD_OK;
 }
 
@@ -816,16 +843,9 @@ int cfd_dt_cfl_dev(cfd_block* const* blocks, int nb, const double* const* Q, dou
     if (!blocks[n] || !Q[n]) return fail(CFD_ERR_ARG, "null block or state");
     if (!blocks[n]->have_metrics) return fail(CFD_ERR_STATE, "cfd_metrics has not been run on a block");
   }
-  cfd_block* b0 = blocks[0];
   int rc = order_on_first(blocks, nb);
   if (rc != CFD_OK) return rc;
-  HIP_TRY(launch_dt_reset(b0->red_dev, b0->stream), "dt reset launch");
-  for (int n = 0; n < nb; ++n) {
-    cfd_block* b = blocks[n];
-    HIP_TRY(launch_dt_max(b->g, Q[n], b->met, b->d.params.gamma, b0->red_dev, b0->stream), "dt launch");
-  }
-  HIP_TRY(launch_dt_finish(b0->red_dev, cfl, dt_dev, b0->stream), "dt finish launch");
-  return CFD_OK;
+  return dt_launches(blocks, nb, Q, cfl, dt_dev);
 }
 
 int cfd_dt_local(cfd_block* const* blocks, int nb, const double* const* Q, double cfl, double* const* dt_field) {
@@ -865,16 +885,16 @@ int cfd_residual(cfd_block* const* blocks, int nb, const double* const* A, const
       return fail(CFD_ERR_ALLOC, "residual scratch");
     }
   }
-  int rc = order_on_first(blocks, nb);
+  int rc = pinned_results(b0);
+  if (rc == CFD_OK) rc = order_on_first(blocks, nb);
   if (rc != CFD_OK) return rc;
   for (int n = 0; n < nb; ++n)
     HIP_TRY(launch_res_partial(blocks[n]->g, A[n], Bm ? Bm[n] : nullptr, scale, b0->res_dev + (int64_t)n * kResGroups * 10,
                                b0->stream),
             "residual launch");
-  double* res_out = b0->res_dev + (int64_t)kMaxBlocks * kResGroups * 10;
-  HIP_TRY(launch_res_final(b0->res_dev, nb * kResGroups, 1.0 / (double)npts, res_out, b0->stream), "residual launch");
-  HIP_TRY(hipMemcpyAsync(out, res_out, 10 * sizeof(double), hipMemcpyDeviceToHost, b0->stream), "copy residual");
+  HIP_TRY(launch_res_final(b0->res_dev, nb * kResGroups, 1.0 / (double)npts, b0->pin, b0->stream), "residual launch");
   HIP_TRY(hipStreamSynchronize(b0->stream), "stream synchronize");
+  std::memcpy(out, b0->pin, 10 * sizeof(double));
   for (int v = 0; v < 10; ++v)
     if (!std::isfinite(out[v])) return fail(CFD_ERR_NONFINITE, "non-finite residual");
   return CFD_OK;

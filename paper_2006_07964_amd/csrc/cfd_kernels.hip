@@ -1769,7 +1769,7 @@ hipError_t launch_dt_max(const Geom& g, const double* q, const double* met, doub
                          hipStream_t s) {
   const int64_t total = (int64_t)g.ni * g.nj * g.nk;
   int bx = (int)((total + 255) / 256);
-  if (bx > 8192) bx = 8192;
+  if (bx > 2048) bx = 2048;  // fills the chip; every workgroup adds an atomic on one address
   hipLaunchKernelGGL(k_dt_max, dim3(bx), dim3(256), 0, s, g, q, met, gamma, acc);
   return hipGetLastError();
 }
@@ -1784,7 +1784,7 @@ __global__ __launch_bounds__(256) void k_finite(Geom g, const double* q, int* fl
     const int64_t p = at(g, i, j, k);
     for (int v = 0; v < 5; ++v) bad |= !isfinite(q[v * g.plane + p]);
   }
-  if (bad) atomicOr(flag, 1);
+  if (bad) *flag = 1;  // every writer stores the same
 }
 
 hipError_t launch_finite(const Geom& g, const double* q, int* flag, hipStream_t s) {
@@ -1829,11 +1829,15 @@ hipError_t launch_dt_local(const Geom& g, const double* q, const double* met, do
   return hipGetLastError();
 }
 
-// ---- CFL time step into device memory (no host round trip) -------------------------
+// ---- CFL time step from the maximum (no host round trip) ------------------------------
 __global__ void k_dt_reset(unsigned long long* acc) { *acc = 0ull; }
 
-__global__ void k_dt_finish(const unsigned long long* acc, double cfl, double* dt) {
+// Leaves the accumulator cleared for the next call, which then needs no launch to clear it (4.6
+// us between two dependent kernels).  The workgroup of k_dt_max that arrives last could do
+// this too, but counting arrivals takes atomics that return (397 workgroups: 7.8 -> 14 us).
+__global__ void k_dt_finish(unsigned long long* acc, double cfl, double* dt) {
   const double smax = __longlong_as_double((long long)*acc);
+  *acc = 0ull;
   *dt = (smax > 0.0 && smax <= 1.7976931348623157e308) ? cfl / smax : __builtin_nan("");
 }
 
@@ -1841,7 +1845,7 @@ hipError_t launch_dt_reset(unsigned long long* acc, hipStream_t s) {
   hipLaunchKernelGGL(k_dt_reset, dim3(1), dim3(1), 0, s, acc);
   return hipGetLastError();
 }
-hipError_t launch_dt_finish(const unsigned long long* acc, double cfl, double* dt, hipStream_t s) {
+hipError_t launch_dt_finish(unsigned long long* acc, double cfl, double* dt, hipStream_t s) {
   hipLaunchKernelGGL(k_dt_finish, dim3(1), dim3(1), 0, s, acc, cfl, dt);
   return hipGetLastError();
 }
@@ -1849,44 +1853,52 @@ hipError_t launch_dt_finish(const unsigned long long* acc, double cfl, double* d
 // ---- residual norms: reduced-dimensional reductions (Sec. 4.5) ------------------------
 // 3D -> lines: each wave walks grid lines (j, k) of the block, its lanes striding along i
 // (coalesced), and keeps per lane the sums of squares and the maxima of the five fields of
-// scale * (a - b) (b may be null); lines -> workgroup: a fixed-order tree in LDS; the
-// kResGroups partial rows of every block are then reduced by one workgroup, again in a
-// fixed order, so the result does not depend on timing.
-__global__ __launch_bounds__(256) void k_res_partial(Geom g, const double* __restrict__ a, const double* __restrict__ b,
-                                                     double scale, double* __restrict__ part) {
-  __shared__ double red[10][256];
+// scale * (a - b) (b may be null); lanes -> wave: a fixed-order shuffle tree; waves ->
+// workgroup: their rows in LDS in order; the kResGroups partial rows of every block are then
+// reduced by one workgroup, again in a fixed order, so the result does not depend on timing.
+// Bound by HBM reads: sixteen waves per workgroup, one workgroup per CU, keep ten loads per
+// lane in flight (four waves did not: 224 x 200 x 176 with b, 348 us at 1.8 TB/s).
+constexpr int kResNT = 1024;
+__global__ __launch_bounds__(kResNT) void k_res_partial(Geom g, const double* __restrict__ a, const double* __restrict__ b,
+                                                        double scale, double* __restrict__ part) {
+  __shared__ double red[kResNT / 64][10];
   double sq[5] = {0, 0, 0, 0, 0}, mx[5] = {0, 0, 0, 0, 0};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lines = g.nj * g.nk;
-  for (int l = blockIdx.x * 4 + wave; l < lines; l += gridDim.x * 4) {
-    const int j = l % g.nj, k = l / g.nj;
+  for (int l = blockIdx.x * (kResNT / 64) + wave; l < lines; l += gridDim.x * (kResNT / 64)) {
+    const int64_t line = at(g, 0, l % g.nj, l / g.nj);
     for (int i = lane; i < g.ni; i += 64) {
-      const int64_t p = at(g, i, j, k);
+      const int64_t p = line + i;
+      double d[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) d[v] = a[v * g.plane + p];
+      if (b) {
+#pragma unroll
+        for (int v = 0; v < 5; ++v) d[v] -= b[v * g.plane + p];
+      }
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        const double d = scale * (b ? a[v * g.plane + p] - b[v * g.plane + p] : a[v * g.plane + p]);
-        sq[v] += d * d;
-        mx[v] = fmax(mx[v], fabs(d));
+        d[v] *= scale;
+        sq[v] += d[v] * d[v];
+        mx[v] = fmax(mx[v], fabs(d[v]));
       }
     }
   }
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
-    red[v][threadIdx.x] = sq[v];
-    red[5 + v][threadIdx.x] = mx[v];
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) {
+      sq[v] += __shfl_down(sq[v], h);
+      mx[v] = fmax(mx[v], __shfl_down(mx[v], h));
+    }
+    if (lane == 0) red[wave][v] = sq[v], red[wave][5 + v] = mx[v];
   }
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) {
-#pragma unroll
-      for (int v = 0; v < 5; ++v) {
-        red[v][threadIdx.x] += red[v][threadIdx.x + h];
-        red[5 + v][threadIdx.x] = fmax(red[5 + v][threadIdx.x], red[5 + v][threadIdx.x + h]);
-      }
-    }
-    __syncthreads();
+  if (threadIdx.x < 10) {
+    double r = red[0][threadIdx.x];
+    for (int w = 1; w < kResNT / 64; ++w) r = threadIdx.x < 5 ? r + red[w][threadIdx.x] : fmax(r, red[w][threadIdx.x]);
+    part[(int64_t)blockIdx.x * 10 + threadIdx.x] = r;
   }
-  if (threadIdx.x < 10) part[(int64_t)blockIdx.x * 10 + threadIdx.x] = red[threadIdx.x][0];
 }
 
 __global__ __launch_bounds__(256) void k_res_final(const double* __restrict__ part, int nparts, double inv_n,
@@ -1922,7 +1934,7 @@ __global__ __launch_bounds__(256) void k_res_final(const double* __restrict__ pa
 
 hipError_t launch_res_partial(const Geom& g, const double* a, const double* b, double scale, double* part,
                               hipStream_t s) {
-  hipLaunchKernelGGL(k_res_partial, dim3(kResGroups), dim3(256), 0, s, g, a, b, scale, part);
+  hipLaunchKernelGGL(k_res_partial, dim3(kResGroups), dim3(kResNT), 0, s, g, a, b, scale, part);
   return hipGetLastError();
 }
 hipError_t launch_res_final(const double* part, int nparts, double inv_n, double* out, hipStream_t s) {
