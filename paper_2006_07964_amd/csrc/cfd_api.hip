@@ -122,6 +122,11 @@ struct ProfScope {
 // and zeta in FP64; 16 x 14 along eta and 16 x 30 (512 threads) along zeta in mixed
 // precision
 constexpr int kDefaultTiles[2][3] = {{5, 6, 6}, {5, 2, 0}};
+// largest block, [FP64 / mixed], whose three sweeps run in one launch.  RK3 step with three
+// launches / one and a sum: FP64 24x24x16 85 / 65 us, 48^3 135 / 123, 64^3 221 / 222, 80x64x64
+// 254 / 252, 80^3 358 / 376 (the three sets of partial sums are extra traffic); mixed 48^3
+// 115 / 101, 80^3 273 / 267, 96x80x72 281 / 276, 96^3 410 / 423
+constexpr int64_t kAllPoints[2] = {300000, 600000};
 
 struct cfd_block {
   cfd_block_desc d;
@@ -130,7 +135,8 @@ struct cfd_block {
   int device = 0;
   double* met = nullptr;  // 10 planes FP64
   void* vis = nullptr;    // 12 planes (compute type)
-  void* rt = nullptr;     // 5 planes (compute type)
+  void* rt = nullptr;     // 5 planes (compute type), 15 where the sweeps run in one launch
+  bool all_sweeps = false;  // small enough for the three sweeps in one launch
   // metrics in the compute type: met itself (FP64), or (mixed) a rounded copy followed by
   // the 9 half-point metric planes of the sweeps
   void* met_r = nullptr;
@@ -454,7 +460,8 @@ int run_visc(cfd_block* b, const double* Q) {
 const char* kSweepNames[3] = {"sweep_xi", "sweep_eta", "sweep_zeta"};
 const char* kSweepRkNames[3] = {"sweep_xi_rk", "sweep_eta_rk", "sweep_zeta_rk"};
 const char* kProfNames[] = {"sweep_xi",    "sweep_eta",    "sweep_zeta",   "sweep_xi_rk", "sweep_eta_rk",
-                            "sweep_zeta_rk", "visc_prepass", "visc_halo", "halo_q",      "halo_visc"};
+                            "sweep_zeta_rk", "visc_prepass", "visc_halo", "halo_q",      "halo_visc",  "sweeps",
+                            "sweeps_rk"};
 
 // run the direction sweeps selected by mask; the last one writes R or the RK stage
 int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, double* out, const double* qn,
@@ -492,6 +499,16 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     ProfScope ps(&b->prof, kSweepNames[0], b->stream);
     hipError_t e = b->d.precision == CFD_FP64 ? launch_sweep<double>(0, a, b->stream, b->cfg[0])
                                               : launch_sweep<float>(0, a, b->stream, b->cfg[0]);
+    ps.done();
+    return e == hipSuccess ? CFD_OK : hip_fail(e, "sweep launch");
+  }
+  if (nd == 3 && inv && b->all_sweeps && !b->own_tiles) {
+    a.b.rt_in = b->rt;
+    a.b.rt_out = b->rt;
+    a.b.out = out;
+    a.c.out_kind = out_kind;
+    ProfScope ps(&b->prof, out_kind == kOutRK ? "sweeps_rk" : "sweeps", b->stream);
+    hipError_t e = b->d.precision == CFD_FP64 ? launch_sweep_all<double>(a, b->stream) : launch_sweep_all<float>(a, b->stream);
     ps.done();
     return e == hipSuccess ? CFD_OK : hip_fail(e, "sweep launch");
   }
@@ -606,12 +623,15 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
   if (b->esize != sizeof(double) && aligned_planes(plane, 10 + 9, b->esize, &b->met_r_raw, &b->met_r))
     return cleanup(CFD_ERR_ALLOC, "metrics allocation");
   if (aligned_planes(plane, 12, b->esize, &b->vis_raw, &b->vis)) return cleanup(CFD_ERR_ALLOC, "viscous scratch allocation");
-  if (aligned_planes(plane, 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
+  b->all_sweeps = d->params.scheme == CFD_AFWENO_MODIFIED && !one_sided_mask(*d) &&
+                  (int64_t)d->ni * d->nj * d->nk <= kAllPoints[b->esize == sizeof(double) ? 0 : 1];
+  if (aligned_planes(plane, b->all_sweeps ? 15 : 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
   if (hipMalloc((void**)&b->red_dev, sizeof(unsigned long long)) != hipSuccess ||
       hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess)
     return cleanup(CFD_ERR_ALLOC, "reduction scratch");
   if (hipEventCreateWithFlags(&b->ev, hipEventDisableTiming) != hipSuccess) return cleanup(CFD_ERR_HIP, "block event");
-  b->bytes = (int64_t)plane * (10 * 8 + (b->esize == sizeof(double) ? 17 : 36) * (int64_t)b->esize);
+  const int planes = (b->esize == sizeof(double) ? 17 : 36) + (b->all_sweeps ? 10 : 0);
+  b->bytes = (int64_t)plane * (10 * 8 + planes * (int64_t)b->esize);
   // block-local viscous halo work
   std::vector<CopySeg> cs;
   std::vector<BcSeg> bs;
@@ -1005,6 +1025,7 @@ struct cfd_batch {
   int cfg[3] = {0, 0, 0};       // tile configuration per direction
   int persist[3] = {0, 0, 0};   // persistent schedule per direction
   bool tuned = false;
+  bool all_sweeps = false;      // the three sweeps of a stage in one launch (the autotuner found it faster)
   float tune_ms[3][kTileCfgs][2];  // autotuner timings (ms per launch, -1: not measured)
   int persist_wgs = 2048;       // workgroups of a persistent launch
   // combined viscous halo work of all blocks: self-periodic + interface copies, ghosts
@@ -1055,7 +1076,7 @@ void fill_tiles(cfd_batch* bt) {
     for (int b = 0; b < nb; ++b) {
       const Geom& g = bt->blocks[b]->g;
       int tc1, td, tlen;
-      sweep_tiling(d, bt->cfg[d], g, &tc1, &td, &tlen);
+      sweep_tiling(d, bt->cfg[d], g, &tc1, &td, &tlen);  // kAllCfg when all_sweeps
       const int n2 = d == 2 ? g.nj : g.nk;
       tl.prefix[b + 1] = tl.prefix[b] + tc1 * td * n2;
     }
@@ -1173,7 +1194,7 @@ void build_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* con
         a.met_r = B->esize == sizeof(double) ? nullptr : static_cast<const float*>(B->met_r);
         a.vis = B->vis;
         a.rt_in = B->rt;
-        a.rt_out = B->rt;
+        a.rt_out = static_cast<char*>(B->rt) + (bt->all_sweeps ? (2 - d) * 5 * B->g.plane * (int64_t)B->esize : 0);
         a.out = d == kSweepOrder[2] ? outp[b] : nullptr;
         a.qn = Qn[b];
         a.dt_field = B->dt_field;
@@ -1196,6 +1217,17 @@ hipError_t launch_batch_sweep(cfd_batch* bt, int st, int d) {
              : launch_sweep_batch<float>(d, bt->cfg[d], bt->persist[d] != 0, a, c, tl, nwg, bt->stream);
 }
 
+// the three sweeps of a stage in one launch, then their sum
+hipError_t launch_batch_all(cfd_batch* bt, int st) {
+  const int nb = (int)bt->blocks.size();
+  int most = 0;
+  for (const cfd_block* B : bt->blocks) most = std::max(most, B->g.ni * B->g.nj * B->g.nk);
+  const SweepBlock* a = bt->sweep_args_dev + st * 3 * nb;
+  const SweepCommon& c = bt->sweep_common[st][kSweepOrder[2]];
+  return bt->precision == CFD_FP64 ? launch_sweep_all_batch<double>(a, c, bt->sweep_tl, most, bt->stream)
+                                   : launch_sweep_all_batch<float>(a, c, bt->sweep_tl, most, bt->stream);
+}
+
 // one RK stage of every block (all launches on bt->stream)
 hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
   const int nb = (int)bt->blocks.size();
@@ -1211,14 +1243,15 @@ hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
       t.p[b] = bt->blocks[b]->vis;
       t.plane[b] = bt->blocks[b]->g.plane;
     }
-    e = bt->precision == CFD_FP64 ? launch_copy<double>(bt->vcopy_dev, bt->nvcopy, bt->maxvcopy, t, bt->stream)
-                                  : launch_copy<float>(bt->vcopy_dev, bt->nvcopy, bt->maxvcopy, t, bt->stream);
-    if (e != hipSuccess) return e;
-    e = bt->precision == CFD_FP64 ? launch_visc_ghost<double>(bt->vbc_dev, bt->nvbc, bt->maxvbc, t, bt->stream)
-                                  : launch_visc_ghost<float>(bt->vbc_dev, bt->nvbc, bt->maxvbc, t, bt->stream);
+    e = bt->precision == CFD_FP64
+            ? launch_visc_halo<double>(bt->vcopy_dev, bt->nvcopy, bt->maxvcopy, bt->vbc_dev, bt->nvbc, bt->maxvbc, t, bt->stream)
+            : launch_visc_halo<float>(bt->vcopy_dev, bt->nvcopy, bt->maxvcopy, bt->vbc_dev, bt->nvbc, bt->maxvbc, t, bt->stream);
     if (e != hipSuccess) return e;
   }
-  for (int n = 0; n < 3 && e == hipSuccess; ++n) e = launch_batch_sweep(bt, st, kSweepOrder[n]);
+  if (bt->all_sweeps)
+    e = launch_batch_all(bt, st);
+  else
+    for (int n = 0; n < 3 && e == hipSuccess; ++n) e = launch_batch_sweep(bt, st, kSweepOrder[n]);
   if (e != hipSuccess) return e;
   // Q halos of every block: wall reset, interface / periodic copies, ghost fills
   BcArgs ba;
@@ -1235,8 +1268,7 @@ hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
   for (int v = 0; v < 5; ++v) ba.qinf[v] = P.qinf[v];
   cfd_exchange* x = bt->x;
   e = launch_wall_reset(x->bc_dev, x->nbc, x->maxbc, ba, bt->stream);
-  if (e == hipSuccess) e = launch_copy<double>(x->q_dev, x->nq, x->maxq, ba.t, bt->stream);
-  if (e == hipSuccess) e = launch_ghost_fill(x->bc_dev, x->nbc, x->maxbc, ba, bt->stream);
+  if (e == hipSuccess) e = launch_halo(x->q_dev, x->nq, x->maxq, x->bc_dev, x->nbc, x->maxbc, ba, bt->stream);
   return e;
 }
 
@@ -1257,6 +1289,7 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
   HIP_TRY(hipEventCreate(&e0), "event");
   HIP_TRY(hipEventCreate(&e1), "event");
   int rc = CFD_OK;
+  float direction_ms[3] = {0.f, 0.f, 0.f};  // fastest sweep of each direction
   if (bt->viscous) {  // the sweeps read the viscous-flux planes of the state being tuned on
     rc = upload_args(bt, Qn, QA, QB, dt_dev);
     if (rc == CFD_OK) {
@@ -1266,6 +1299,20 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
       if (e != hipSuccess) rc = hip_fail(e, "tuning prepass");
     }
   }
+  // milliseconds of two launches after one that warms caches and code
+  auto timed = [&](auto&& launch) {
+    float ms = 0.f, total = 0.f;
+    for (int rep = 0; rep < 3 && rc == CFD_OK; ++rep) {
+      hipError_t e = hipEventRecord(e0, bt->stream);
+      if (e == hipSuccess) e = launch();
+      if (e == hipSuccess) e = hipEventRecord(e1, bt->stream);
+      if (e == hipSuccess) e = hipEventSynchronize(e1);
+      if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+      if (e != hipSuccess) rc = hip_fail(e, "tuning launch");
+      if (rep > 0) total += ms;
+    }
+    return total;
+  };
   for (int d = 0; d < 3 && rc == CFD_OK; ++d) {
     float best = 1e30f;
     int best_cfg = 0, best_p = 0;
@@ -1277,16 +1324,7 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
         bt->persist[d] = p;
         fill_tiles(bt);
         if ((rc = upload_args(bt, Qn, QA, QB, dt_dev)) != CFD_OK) break;
-        float ms = 0.f, total = 0.f;
-        for (int rep = 0; rep < 3 && rc == CFD_OK; ++rep) {
-          hipError_t e = hipEventRecord(e0, bt->stream);
-          if (e == hipSuccess) e = launch_batch_sweep(bt, 0, d);
-          if (e == hipSuccess) e = hipEventRecord(e1, bt->stream);
-          if (e == hipSuccess) e = hipEventSynchronize(e1);
-          if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-          if (e != hipSuccess) rc = hip_fail(e, "tuning launch");
-          if (rep > 0) total += ms;  // first launch warms caches and code
-        }
+        const float total = timed([&]() { return launch_batch_sweep(bt, 0, d); });
         if (rc == CFD_OK) bt->tune_ms[d][c][p] = total / 2;
         if (rc == CFD_OK && total < best) {
           best = total;
@@ -1296,6 +1334,28 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
       }
     bt->cfg[d] = best_cfg;
     bt->persist[d] = best_p;
+    direction_ms[d] = best;
+  }
+  // the three sweeps of small blocks in one launch, against the fastest three
+  bool all = rc == CFD_OK;
+  for (const cfd_block* B : bt->blocks) all = all && B->all_sweeps;
+  if (all) {
+    int cfg[3], persist[3];
+    for (int d = 0; d < 3; ++d) {
+      cfg[d] = bt->cfg[d];
+      persist[d] = bt->persist[d];
+      bt->cfg[d] = kAllCfg[bt->precision == CFD_FP64 ? 0 : 1][d];
+      bt->persist[d] = 0;
+    }
+    bt->all_sweeps = true;
+    fill_tiles(bt);
+    rc = upload_args(bt, Qn, QA, QB, dt_dev);
+    float total = 0.f;
+    if (rc == CFD_OK) total = timed([&]() { return launch_batch_all(bt, 0); });
+    if (rc != CFD_OK || total >= direction_ms[0] + direction_ms[1] + direction_ms[2]) {
+      bt->all_sweeps = false;
+      for (int d = 0; d < 3; ++d) bt->cfg[d] = cfg[d], bt->persist[d] = persist[d];
+    }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -1384,6 +1444,7 @@ int batch_set_tuning(cfd_batch* bt, const int* cfg, const int* persist) {
     bt->cfg[d] = cfg[d];
     bt->persist[d] = persist[d] != 0;
   }
+  bt->all_sweeps = false;
   fill_tiles(bt);
   bt->tuned = true;
   bt->key.clear();  // recapture with the new tiling
@@ -1631,8 +1692,7 @@ int cfd_halo_exchange(cfd_exchange* x, int field_set, void* const* block_bufs, v
     Profiler* prof = &x->blocks[0]->prof;
     ProfScope ps(prof, "halo_q", s);
     hipError_t e = launch_wall_reset(x->bc_dev, x->nbc, x->maxbc, ba, s);
-    if (e == hipSuccess) e = launch_copy<double>(x->q_dev, x->nq, x->maxq, t, s);
-    if (e == hipSuccess) e = launch_ghost_fill(x->bc_dev, x->nbc, x->maxbc, ba, s);
+    if (e == hipSuccess) e = launch_halo(x->q_dev, x->nq, x->maxq, x->bc_dev, x->nbc, x->maxbc, ba, s);
     ps.done();
     return e == hipSuccess ? CFD_OK : hip_fail(e, "halo exchange (Q)");
   }

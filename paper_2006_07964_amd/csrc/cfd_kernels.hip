@@ -1264,6 +1264,145 @@ template hipError_t launch_sweep_batch<float>(int, int, bool, const SweepBlock*,
                                               hipStream_t);
 
 // =====================================================================================
+// The three direction sweeps of small blocks in one launch.  Their partial sums are
+// independent, so one grid covers the tiles of zeta, then eta, then xi, each direction writing
+// its own five planes, and a second launch adds them in the order of the sequential sweeps and
+// writes R or the RK stage: two dependent launches instead of three, and three times the
+// workgroups at once for blocks that do not fill the chip.  A launch that waits for another
+// costs 3-4 us before its own work; a sweep of 32^3 takes 6-7 us with that.
+// =====================================================================================
+template <typename R>
+constexpr int kAllTW = sizeof(R) == 8 ? 8 : 16;  // eta and zeta tiles (configurations 6 and 2)
+template <typename R>
+constexpr int kAllTS = sizeof(R) == 8 ? 30 : 14;
+constexpr int kAllNT = 256;
+
+template <typename R>
+union AllShared {
+  SweepShared<R, 4, 58> xi;  // configuration 5
+  SweepShared<R, kAllTW<R>, kAllTS<R>> across;
+};
+
+// blocks.b[d]: arguments and tiling of direction d; zeta has tiles [0, nz), eta the next ne
+template <typename R>
+__global__ __launch_bounds__(kAllNT) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_all(SweepCommon c, AllBlocks a,
+                                                                                             int nz, int ne) {
+  __shared__ AllShared<R> sh;
+  const int t = blockIdx.x;
+  if (t < nz)
+    sweep_tile<2, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, a.b[2], xcd_remap(t, nz), sh.across);
+  else if (t < nz + ne)
+    sweep_tile<1, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, a.b[1], xcd_remap(t - nz, ne), sh.across);
+  else
+    sweep_tile<0, R, 4, 58, kAllNT>(c, a.b[0], xcd_remap(t - nz - ne, gridDim.x - nz - ne), sh.xi);
+}
+
+// blocks + 2 * nblk .. of zeta, + nblk .. of eta, + 0 .. of xi
+template <typename R>
+__global__ __launch_bounds__(kAllNT) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_all_batch(
+    const SweepBlock* __restrict__ blocks, SweepCommon c, TileList tx, TileList te, TileList tz) {
+  __shared__ AllShared<R> sh;
+  const int nb = tx.nblk, nz = tz.prefix[nb], ne = te.prefix[nb];
+  int t = blockIdx.x, blk = 0;
+  if (t < nz) {
+    while (t >= tz.prefix[blk + 1]) ++blk;
+    sweep_tile<2, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, blocks[2 * nb + blk], t - tz.prefix[blk], sh.across);
+  } else if (t < nz + ne) {
+    t -= nz;
+    while (t >= te.prefix[blk + 1]) ++blk;
+    sweep_tile<1, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, blocks[nb + blk], t - te.prefix[blk], sh.across);
+  } else {
+    t -= nz + ne;
+    while (t >= tx.prefix[blk + 1]) ++blk;
+    sweep_tile<0, R, 4, 58, kAllNT>(c, blocks[blk], t - tx.prefix[blk], sh.xi);
+  }
+}
+
+// R or the RK stage from the three partial sums (b: the xi block; rt: zeta's five planes, then
+// eta's, then xi's)
+template <typename R>
+__device__ __forceinline__ void combine_block(const SweepCommon& c, const SweepBlock& b) {
+  const Geom& g = b.g;
+  const GP<const R> rt = (GP<const R>)to_global(static_cast<const R*>(b.rt_in));
+  const int total = g.ni * g.nj * g.nk;
+  for (int e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
+    const int i = e % g.ni, jk = e / g.ni;
+    const uint32_t p = (uint32_t)at(g, i, jk % g.nj, jk / g.nj);
+    R r[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+      r[v] = ldg(plane_ptr(rt, (10 + v) * g.plane), p) +
+             (ldg(plane_ptr(rt, (5 + v) * g.plane), p) + ldg(plane_ptr(rt, v * g.plane), p));
+    const double Jo = ldg(plane_ptr(to_global(b.met), 9 * g.plane), p);
+    const GP<double> out = to_global(b.out);
+    if (c.out_kind == kOutRhs) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) stg(plane_ptr(out, v * g.plane), p, Jo * double(r[v]));
+    } else {
+      double qno[5], qco[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        qco[v] = ldg(plane_ptr(to_global(b.q), v * g.plane), p);
+        qno[v] = b.qn == b.q ? qco[v] : ldg(plane_ptr(to_global(b.qn), v * g.plane), p);
+      }
+      const double dt = b.dt_field ? ldg(to_global(b.dt_field), p) : c.dt_dev ? *c.dt_dev : c.dt;
+      const double cdt = c.cc * dt * Jo;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) stg(plane_ptr(out, v * g.plane), p, c.ca * qno[v] + c.cb * qco[v] + cdt * double(r[v]));
+    }
+  }
+}
+template <typename R>
+__global__ __launch_bounds__(256) void k_combine(SweepCommon c, SweepBlock b) {
+  combine_block<R>(c, b);
+}
+template <typename R>
+__global__ __launch_bounds__(256) void k_combine_batch(const SweepBlock* __restrict__ blocks, SweepCommon c) {
+  combine_block<R>(c, blocks[blockIdx.y]);
+}
+
+template <typename R>
+hipError_t launch_sweep_all(const SweepArgs& a, hipStream_t s) {
+  const Geom& g = a.b.g;
+  SweepCommon part = a.c;
+  part.has_prev = 0;
+  part.out_kind = kOutPartial;
+  AllBlocks all;
+  int n[3];
+  for (int d = 0; d < 3; ++d) {
+    SweepBlock& b = all.b[d] = a.b;
+    sweep_tiling(d, kAllCfg[sizeof(R) == 8 ? 0 : 1][d], g, &b.tiles_c1, &b.tiles_d, &b.tile_len);
+    n[d] = b.tiles_c1 * b.tiles_d * (d == 2 ? g.nj : g.nk);
+    b.rt_out = static_cast<R*>(a.b.rt_out) + (2 - d) * 5 * g.plane;
+  }
+  hipLaunchKernelGGL((k_sweep_all<R>), dim3(n[0] + n[1] + n[2]), dim3(kAllNT), 0, s, part, all, n[2], n[1]);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int total = g.ni * g.nj * g.nk;
+  hipLaunchKernelGGL((k_combine<R>), dim3((total + 255) / 256), dim3(256), 0, s, a.c, a.b);
+  return hipGetLastError();
+}
+template hipError_t launch_sweep_all<double>(const SweepArgs&, hipStream_t);
+template hipError_t launch_sweep_all<float>(const SweepArgs&, hipStream_t);
+
+template <typename R>
+hipError_t launch_sweep_all_batch(const SweepBlock* blocks, const SweepCommon& c, const TileList tl[3], int max_points,
+                                  hipStream_t s) {
+  const int nb = tl[0].nblk;
+  SweepCommon part = c;
+  part.has_prev = 0;
+  part.out_kind = kOutPartial;
+  const int n = tl[0].prefix[nb] + tl[1].prefix[nb] + tl[2].prefix[nb];
+  hipLaunchKernelGGL((k_sweep_all_batch<R>), dim3(n), dim3(kAllNT), 0, s, blocks, part, tl[0], tl[1], tl[2]);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_combine_batch<R>), dim3((max_points + 255) / 256, nb), dim3(256), 0, s, blocks, c);
+  return hipGetLastError();
+}
+template hipError_t launch_sweep_all_batch<double>(const SweepBlock*, const SweepCommon&, const TileList[3], int, hipStream_t);
+template hipError_t launch_sweep_all_batch<float>(const SweepBlock*, const SweepCommon&, const TileList[3], int, hipStream_t);
+
+// =====================================================================================
 // Marching sweep (FP64, eta and zeta, partial sums): one thread per grid line, lanes along i.
 //
 // A thread walks its line of nodes through a chunk of `len` outputs.  At node p it adds the
@@ -1546,8 +1685,7 @@ bool launch_march(int dir, const SweepArgs& a, hipStream_t s, hipError_t* err) {
 // layer m-1 inside the source face), boundary fills.
 // =====================================================================================
 template <typename T>
-__global__ __launch_bounds__(256) void k_copy(const CopySeg* segs, PtrTable t) {
-  const CopySeg S = segs[blockIdx.y];
+__device__ __forceinline__ void copy_segment(const CopySeg& S, const PtrTable& t) {
   const int per_plane = S.na * S.nb * kHalo;
   const int total = per_plane * S.nplanes;
   T* dst = static_cast<T*>(t.p[S.dst]);
@@ -1572,6 +1710,11 @@ __global__ __launch_bounds__(256) void k_copy(const CopySeg* segs, PtrTable t) {
     const T x = src[(S.src_plane0 + vv) * ps + S.src_off + a * S.src_sa + b * S.src_sb + l * S.src_sl];
     dst[(S.plane0 + vv) * pd + S.dst_off + a * S.dst_sa + b * S.dst_sb + l * S.dst_sl] = S.negate ? -x : x;
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_copy(const CopySeg* segs, PtrTable t) {
+  copy_segment<T>(segs[blockIdx.y], t);
 }
 
 template <typename T>
@@ -1638,8 +1781,7 @@ __device__ void char_farfield(const double qb[5], const double n[3], const doubl
   qg[4] = p / gm1 + 0.5 * rho * (u * u + v * v + w * w);
 }
 
-__global__ __launch_bounds__(256) void k_ghost_fill(const BcSeg* segs, BcArgs A) {
-  const BcSeg S = segs[blockIdx.y];
+__device__ __forceinline__ void ghost_segment(const BcSeg& S, const BcArgs& A) {
   double* Q = static_cast<double*>(A.t.p[S.blk]);
   const int64_t pl = A.t.plane[S.blk];
   const int64_t total = (int64_t)S.na * S.nb * kHalo;
@@ -1682,8 +1824,7 @@ __global__ __launch_bounds__(256) void k_ghost_fill(const BcSeg* segs, BcArgs A)
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_visc_ghost(const BcSeg* segs, PtrTable t) {
-  const BcSeg S = segs[blockIdx.y];
+__device__ __forceinline__ void visc_ghost_segment(const BcSeg& S, const PtrTable& t) {
   T* V = static_cast<T*>(t.p[S.blk]);
   const int64_t pl = t.plane[S.blk];
   const int64_t total = (int64_t)S.na * S.nb * kHalo * 4;
@@ -1700,6 +1841,26 @@ __global__ __launch_bounds__(256) void k_visc_ghost(const BcSeg* segs, PtrTable 
   }
 }
 
+// Halo copies and ghost fills in one launch: both read nodes of the blocks and write halo nodes
+// beyond different rectangles of their faces, so neither waits for the other.
+__global__ __launch_bounds__(256) void k_halo(const CopySeg* copies, int ncopy, const BcSeg* bcs, BcArgs A) {
+  if ((int)blockIdx.y < ncopy)
+    copy_segment<double>(copies[blockIdx.y], A.t);
+  else
+    ghost_segment(bcs[blockIdx.y - ncopy], A);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_visc_halo(const CopySeg* copies, int ncopy, const BcSeg* bcs, PtrTable t) {
+  if ((int)blockIdx.y < ncopy)
+    copy_segment<T>(copies[blockIdx.y], t);
+  else
+    visc_ghost_segment<T>(bcs[blockIdx.y - ncopy], t);
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_visc_ghost(const BcSeg* segs, PtrTable t) {
+  visc_ghost_segment<T>(segs[blockIdx.y], t);
+}
+
 static dim3 bc_grid(int max_elems, int nseg) {
   int bx = (max_elems + 255) / 256;
   if (bx > 256) bx = 256;  // grid-stride: more workgroups mostly idle on short segments
@@ -1712,11 +1873,23 @@ hipError_t launch_wall_reset(const BcSeg* segs_dev, int nseg, int max_elems, con
   hipLaunchKernelGGL(k_wall_reset, bc_grid(max_elems, nseg), dim3(256), 0, s, segs_dev, a);
   return hipGetLastError();
 }
-hipError_t launch_ghost_fill(const BcSeg* segs_dev, int nseg, int max_elems, const BcArgs& a, hipStream_t s) {
-  if (nseg == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_ghost_fill, bc_grid(max_elems * kHalo, nseg), dim3(256), 0, s, segs_dev, a);
+hipError_t launch_halo(const CopySeg* copies, int ncopy, int max_copy, const BcSeg* bcs, int nbc, int max_bc,
+                       const BcArgs& a, hipStream_t s) {
+  if (nbc == 0) return launch_copy<double>(copies, ncopy, max_copy, a.t, s);
+  const int most = ncopy && max_copy > max_bc * kHalo ? max_copy : max_bc * kHalo;
+  hipLaunchKernelGGL(k_halo, bc_grid(most, ncopy + nbc), dim3(256), 0, s, copies, ncopy, bcs, a);
   return hipGetLastError();
 }
+template <typename T>
+hipError_t launch_visc_halo(const CopySeg* copies, int ncopy, int max_copy, const BcSeg* bcs, int nbc, int max_bc,
+                            const PtrTable& t, hipStream_t s) {
+  if (nbc == 0) return launch_copy<T>(copies, ncopy, max_copy, t, s);
+  const int most = ncopy && max_copy > max_bc * kHalo * 4 ? max_copy : max_bc * kHalo * 4;
+  hipLaunchKernelGGL(k_visc_halo<T>, bc_grid(most, ncopy + nbc), dim3(256), 0, s, copies, ncopy, bcs, t);
+  return hipGetLastError();
+}
+template hipError_t launch_visc_halo<double>(const CopySeg*, int, int, const BcSeg*, int, int, const PtrTable&, hipStream_t);
+template hipError_t launch_visc_halo<float>(const CopySeg*, int, int, const BcSeg*, int, int, const PtrTable&, hipStream_t);
 template <typename T>
 hipError_t launch_visc_ghost(const BcSeg* segs_dev, int nseg, int max_elems, const PtrTable& t, hipStream_t s) {
   if (nseg == 0) return hipSuccess;

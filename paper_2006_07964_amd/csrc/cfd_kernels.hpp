@@ -110,6 +110,20 @@ int sweep_threads(int cfg);
 template <typename R>
 hipError_t launch_sweep(int dir, SweepArgs a, hipStream_t s, int cfg = 0);
 
+// All three sweeps of a small block (modified scheme, no one-sided closure) in one launch into
+// three sets of partial sums (rt_in = rt_out: 15 planes), and a launch that adds them and
+// writes R or the RK stage
+struct AllBlocks {
+  SweepBlock b[3];
+};
+constexpr int kAllCfg[2][3] = {{5, 6, 6}, {5, 2, 2}};  // tile configurations [FP64 / mixed][direction]
+template <typename R>
+hipError_t launch_sweep_all(const SweepArgs& a, hipStream_t s);
+// blocks: nb xi blocks, nb eta, nb zeta, tiled by kAllCfg (tl likewise); c of the xi sweep
+template <typename R>
+hipError_t launch_sweep_all_batch(const SweepBlock* blocks, const SweepCommon& c, const TileList tl[3], int max_points,
+                                  hipStream_t s);
+
 // FP64 xi sweep of the modified scheme, one wave per line
 hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s);
 
@@ -155,7 +169,12 @@ struct BcArgs {
   double qinf[5];
 };
 hipError_t launch_wall_reset(const BcSeg* segs_dev, int nseg, int max_elems, const BcArgs& a, hipStream_t s);
-hipError_t launch_ghost_fill(const BcSeg* segs_dev, int nseg, int max_elems, const BcArgs& a, hipStream_t s);
+// halo copies and ghost fills (of the parts of faces no copy covers) in one launch
+hipError_t launch_halo(const CopySeg* copies, int ncopy, int max_copy, const BcSeg* bcs, int nbc, int max_bc,
+                       const BcArgs& a, hipStream_t s);
+template <typename T>
+hipError_t launch_visc_halo(const CopySeg* copies, int ncopy, int max_copy, const BcSeg* bcs, int nbc, int max_bc,
+                            const PtrTable& t, hipStream_t s);
 template <typename T>
 hipError_t launch_visc_ghost(const BcSeg* segs_dev, int nseg, int max_elems, const PtrTable& t, hipStream_t s);
 
