@@ -524,7 +524,7 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     hipError_t e = hipSuccess;
     if (b->d.precision != CFD_FP64)
       e = launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
-    else if (!b->own_tiles && dirs[n] == 0 && inv && a.c.ph.scheme == CFD_AFWENO_MODIFIED)
+    else if (!b->own_tiles && dirs[n] == 0 && inv)
       e = launch_sweep_rows(a, b->stream);
     else if (b->own_tiles || !launch_march(dirs[n], a, b->stream, &e))
       e = launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]]);

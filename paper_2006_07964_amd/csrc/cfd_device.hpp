@@ -462,6 +462,61 @@ __device__ __forceinline__ void weno_diff(R D1, R D2, R D3, R D4, R eps4, bool l
   cr = nr * (dl * inv);
 }
 
+// weno_left's value the same way: eight times the left-biased value at i+1/2 minus the centre
+// value.  The right-biased value at i-1/2 is this of (-D4, -D3, -D2, -D1).
+template <typename R>
+__device__ __forceinline__ R weno_left_diff(R D1, R D2, R D3, R D4, R eps4, bool linear) {
+  const R d0 = D2 - D1, e0 = R(3) * D2 - D1;
+  const R d1 = D3 - D2, e1 = -(D2 + D3);
+  const R d2 = D4 - D3, e2 = D4 - R(3) * D3;
+  const R A0 = d0 + R(2) * e0, A1 = d1 - R(2) * e1, A2 = d2 - R(2) * e2;
+  if (linear) return (A0 + R(10) * A1 + R(5) * A2) * R(1.0 / 16.0);
+  const R t0 = R(13.0 / 3.0) * d0 * d0 + (e0 * e0 + eps4);
+  const R t1 = R(13.0 / 3.0) * d1 * d1 + (e1 * e1 + eps4);
+  const R t2 = R(13.0 / 3.0) * d2 * d2 + (e2 * e2 + eps4);
+  const R s0 = t0 * t0, s1 = t1 * t1, s2 = t2 * t2;
+  const R q0 = s1 * s2, q1 = R(10) * (s0 * s2), q2 = R(5) * (s0 * s1);
+  return (q0 * A0 + q1 * A1 + q2 * A2) * rcp(q0 + q1 + q2);
+}
+
+// q + R V / 8 in conserved variables, for a space that does not sit at the state q
+template <typename R>
+__device__ __forceinline__ void unproject_diff(const NodeSpace<R>& B, const Gas<R>& G, const R V[5], const R q[5], R out[5]) {
+  const R sp = V[3] + V[4], sm = (V[3] - V[4]) * R(0.70710678118654752440);
+  const R kv = B.rkx * V[0] + B.rky * V[1] + B.rkz * V[2];
+  const R yr = B.rho8 * kv + B.a8 * sp;
+  const R yu = B.rr8 * (B.rky * V[2] - B.rkz * V[1] + B.rkx * sm);
+  const R yv = B.rr8 * (B.rkz * V[0] - B.rkx * V[2] + B.rky * sm);
+  const R yw = B.rr8 * (B.rkx * V[1] - B.rky * V[0] + B.rkz * sm);
+  out[0] = q[0] + yr;
+  out[1] = q[1] + (B.u * yr + yu);
+  out[2] = q[2] + (B.v * yr + yv);
+  out[3] = q[3] + (B.w * yr + yw);
+  out[4] = q[4] + (B.ke * yr + (B.u * yu + B.v * yv + B.w * yw) + (B.b8 * sp) * G.gm1inv);
+}
+
+// Steger-Warming flux of one sign of a state in primitive variables (rinv = 1 / rho) through
+// the hatted metric (mx, my, mz) of magnitude mag = 1 / minv
+template <int SIGN, typename R>
+__device__ __forceinline__ void prim_flux(R rho, R rinv, R u, R v, R w, R p, const Gas<R>& G, R mx, R my, R mz, R mag, R minv,
+                                          R F[5]) {
+  const R c2 = G.gamma * p * rinv;
+  const R c = c2 * rsq(c2);
+  const R ke = R(0.5) * (u * u + v * v + w * w);
+  const R mu = mx * u + my * v + mz * w;
+  const R l4 = mu + mag * c, l5 = mu - mag * c;
+  // twice the split eigenvalues; f carries the half
+  const R a1 = mu + R(SIGN) * fabs(mu), a4 = l4 + R(SIGN) * fabs(l4), a5 = l5 + R(SIGN) * fabs(l5);
+  const R f = rho * (R(0.5) * G.inv2g);
+  const R s45 = a4 + a5;
+  const R fd = f * ((a4 - a5) * (c * minv));
+  F[0] = f * ((R(2) * G.gm1) * a1 + s45);
+  F[1] = F[0] * u + fd * mx;
+  F[2] = F[0] * v + fd * my;
+  F[3] = F[0] * w + fd * mz;
+  F[4] = F[0] * ke + (f * s45) * (c2 * G.gm1inv) + fd * mu;
+}
+
 // Steger-Warming flux of one sign at a half point whose state is the node's plus R V / 8,
 // through the hatted metric (mx, my, mz) of magnitude mag = 1 / minv.  With du the velocity
 // increment, p = p_node + (rho c / sqrt2)(V3 + V4) / 8 - (gamma-1) rho |du|^2 / 2 exactly.
@@ -478,21 +533,16 @@ __device__ __forceinline__ void half_flux(const NodeSpace<R>& B, const Gas<R>& G
   const R dw = g * (B.rkx * V[1] - B.rky * V[0] + B.rkz * sm);
   const R u = B.u + du, v = B.v + dv, w = B.w + dw;
   const R p = (B.b8 * sp + B.p) - (R(0.5) * G.gm1 * rho) * (du * du + dv * dv + dw * dw);
-  const R c2 = G.gamma * p * rinv;
-  const R c = c2 * rsq(c2);
-  const R ke = R(0.5) * (u * u + v * v + w * w);
-  const R mu = mx * u + my * v + mz * w;
-  const R l4 = mu + mag * c, l5 = mu - mag * c;
-  // twice the split eigenvalues; f carries the half
-  const R a1 = mu + R(SIGN) * fabs(mu), a4 = l4 + R(SIGN) * fabs(l4), a5 = l5 + R(SIGN) * fabs(l5);
-  const R f = rho * (R(0.5) * G.inv2g);
-  const R s45 = a4 + a5;
-  const R fd = f * ((a4 - a5) * (c * minv));
-  F[0] = f * ((R(2) * G.gm1) * a1 + s45);
-  F[1] = F[0] * u + fd * mx;
-  F[2] = F[0] * v + fd * my;
-  F[3] = F[0] * w + fd * mz;
-  F[4] = F[0] * ke + (f * s45) * (c2 * G.gm1inv) + fd * mu;
+  prim_flux<SIGN>(rho, rinv, u, v, w, p, G, mx, my, mz, mag, minv, F);
+}
+
+// the same of a conserved state
+template <int SIGN, typename R>
+__device__ __forceinline__ void state_flux(const R q[5], const Gas<R>& G, R mx, R my, R mz, R mag, R minv, R F[5]) {
+  const R rinv = rcp(q[0]);
+  const R u = q[1] * rinv, v = q[2] * rinv, w = q[3] * rinv;
+  const R p = G.gm1 * (q[4] - R(0.5) * (q[1] * u + q[2] * v + q[3] * w));
+  prim_flux<SIGN>(q[0], rinv, u, v, w, p, G, mx, my, mz, mag, minv, F);
 }
 
 // ---- sixth-order half-point interpolation of node metrics ---------------------------

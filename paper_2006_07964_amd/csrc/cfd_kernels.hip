@@ -195,6 +195,18 @@ __device__ __forceinline__ double os6_weight(int row, int sign, int m) {
   return sign > 0 ? kOS6[row][m] : -kOS6[row][6 - m];
 }
 
+// The weight table in LDS, for kernels whose lanes look up different rows (a load from memory
+// for each of seven dependent terms held up every tile next to a wall).  Every thread of the
+// workgroup calls it before a barrier.
+template <typename R>
+__device__ __forceinline__ void os6_stage(R* tab) {
+  if (threadIdx.x < 21) tab[threadIdx.x] = R(kOS6[threadIdx.x / 7][threadIdx.x % 7]);
+}
+template <typename R>
+__device__ __forceinline__ R os6_weight(const R* tab, int row, int sign, int m) {
+  return sign > 0 ? tab[row * 7 + m] : -tab[row * 7 + 6 - m];
+}
+
 // d/dn of a field on a 7-point line, g(m) = value at offset m (sixth-order central)
 template <typename R, typename F>
 __device__ __forceinline__ R grad6(F g) {
@@ -246,6 +258,8 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
   const GP<const R> met = to_global(static_cast<const R*>(a.met_r));
   const GP<R> out = to_global(static_cast<R*>(a.vis));
   const int64_t plane = g.plane;
+  __shared__ R os_tab[OS ? 21 : 1];
+  if constexpr (OS) os6_stage(os_tab);  // the barrier of the first plane orders it
   R P[7][4];  // own column, planes k-3 .. k+3
   if (own) {
 #pragma unroll
@@ -277,7 +291,9 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
       if constexpr (OS) {
         // nodes next to a one-sided face of direction d: the seven-point one-sided
         // derivative over the nodes nearest the face replaces the central one (whose
-        // ghost values it ignores); primitives of the window nodes from Q
+        // ghost values it ignores).  Along xi and eta the LDS plane holds the window's
+        // primitives (unless a last tile has fewer than four columns or rows), else they
+        // come from Q, whose loads one after the other would hold up the whole tile
         const int idx[3] = {i, j, k};
         const int nds[3] = {g.ni, g.nj, g.nk};
         const uint32_t st[3] = {1u, (uint32_t)g.ld_i, sk};
@@ -286,13 +302,25 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
           int first, row, sign;
           if (!one_sided_window((a.one_sided >> (2 * d)) & 3, idx[d], nds[d], &first, &row, &sign)) continue;
           R acc[4] = {R(0), R(0), R(0), R(0)};
+          const int at0 = first - (d == 0 ? i0 : j0) + 3;  // the window in the LDS plane
+          if (d < 2 && at0 >= 0 && at0 + 6 < (d == 0 ? VI : VJ) + 6) {
+            const R* w0 = d == 0 ? &sp[0][tj + 3][at0] : &sp[0][at0][ti + 3];
+            const int next = d == 0 ? 1 : VI + 6;
 #pragma unroll 1
-          for (int m = 0; m < 7; ++m) {
-            R pr[4];
-            primitives<R>(Q, plane, p + (uint32_t)(first + m - idx[d]) * st[d], gg, pr);
-            const R wgt = R(os6_weight(row, sign, m));
+            for (int m = 0; m < 7; ++m) {
+              const R wgt = os6_weight(os_tab, row, sign, m);
 #pragma unroll
-            for (int n = 0; n < 4; ++n) acc[n] += wgt * pr[n];
+              for (int n = 0; n < 4; ++n) acc[n] += wgt * w0[n * (VJ + 6) * (VI + 6) + m * next];
+            }
+          } else {
+#pragma unroll 1
+            for (int m = 0; m < 7; ++m) {
+              R pr[4];
+              primitives<R>(Q, plane, p + (uint32_t)(first + m - idx[d]) * st[d], gg, pr);
+              const R wgt = os6_weight(os_tab, row, sign, m);
+#pragma unroll
+              for (int n = 0; n < 4; ++n) acc[n] += wgt * pr[n];
+            }
           }
 #pragma unroll
           for (int n = 0; n < 4; ++n) gr[n][d] = acc[n];
@@ -669,6 +697,11 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
     }
   };
 
+  __shared__ R os_tab[OS ? 21 : 1];
+  if constexpr (OS) {
+    os6_stage(os_tab);
+    __syncthreads();
+  }
   if (c.do_inv) {
     // ---- stage Q (compute type) and the sweep direction's node metrics (FP64) of nodes
     // d0-3 .. d0+ts+2 of the tile's lines in LDS; sFn holds Q until the nodal fluxes
@@ -844,45 +877,73 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
       const int s = node_of(tid, NH), w = line_of(tid, NH);
       if (tid < LINES * NH && s <= ts && c1_0 + w < n1 && d0 - 1 + s <= nd - 1) {
         const int sc = s + 2;
-        // half-point metric: read from LDS in mixed precision; in FP64 formed again where it
-        // is used rather than held in registers
-        auto hm = [&](int c) {
-          if constexpr (kHalfPre<R>) {
-            return sH[L::f(c, w, s, NH)];
-          } else {
-            return R(half_metric([&](int m) { return sM[L::f(c, w, sc + m, NN)]; }));
-          }
-        };
         R qa[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) qa[v] = R(0.5) * (R(sFn[L::f(v, w, sc, NN)]) + R(sFn[L::f(v, w, sc + 1, NN)]));
-        const Basis<R> B = make_basis(qa, hm(0), hm(1), hm(2), G);
-        // V[t][field] at node n + t - 2; node n+3 replaces node n-2 once the left value is
-        // formed, which keeps five stencil points live instead of six
-        R V[5][5];
-        auto proj = [&](int tt, R out[5]) {
-          R qq[5];
-#pragma unroll
-          for (int v = 0; v < 5; ++v) qq[v] = R(sFn[L::f(v, w, s + tt, NN)]);
-          project(B, G, qq, out);
-        };
-#pragma unroll
-        for (int tt = 0; tt < 5; ++tt) proj(tt, V[tt]);
-        R vl[5], vr[5], uh[5], F[5];
-#pragma unroll
-        for (int f = 0; f < 5; ++f) vl[f] = weno_left(V[0][f], V[1][f], V[2][f], V[3][f], V[4][f], eps, linear);
-        proj(5, V[0]);
-#pragma unroll
-        for (int f = 0; f < 5; ++f) vr[f] = weno_left(V[0][f], V[4][f], V[3][f], V[2][f], V[1][f], eps, linear);
         // this thread alone writes slot s: F+ goes to LDS, F- is added to it
-        unproject(B, G, vl, uh);
-        sw_flux<+1>(uh, hm(0), hm(1), hm(2), G, F);
+        if constexpr (kHalfPre<R>) {
+          auto hm = [&](int c) { return sH[L::f(c, w, s, NH)]; };
+          const Basis<R> B = make_basis(qa, hm(0), hm(1), hm(2), G);
+          // V[t][field] at node n + t - 2; node n+3 replaces node n-2 once the left value is
+          // formed, which keeps five stencil points live instead of six
+          R V[5][5];
+          auto proj = [&](int tt, R out[5]) {
+            R qq[5];
 #pragma unroll
-        for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] = F[v];
-        unproject(B, G, vr, uh);
-        sw_flux<-1>(uh, hm(0), hm(1), hm(2), G, F);
+            for (int v = 0; v < 5; ++v) qq[v] = R(sFn[L::f(v, w, s + tt, NN)]);
+            project(B, G, qq, out);
+          };
 #pragma unroll
-        for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] += F[v];
+          for (int tt = 0; tt < 5; ++tt) proj(tt, V[tt]);
+          R vl[5], vr[5], uh[5], F[5];
+#pragma unroll
+          for (int f = 0; f < 5; ++f) vl[f] = weno_left(V[0][f], V[1][f], V[2][f], V[3][f], V[4][f], eps, linear);
+          proj(5, V[0]);
+#pragma unroll
+          for (int f = 0; f < 5; ++f) vr[f] = weno_left(V[0][f], V[4][f], V[3][f], V[2][f], V[1][f], eps, linear);
+          unproject(B, G, vl, uh);
+          sw_flux<+1>(uh, hm(0), hm(1), hm(2), G, F);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] = F[v];
+          unproject(B, G, vr, uh);
+          sw_flux<-1>(uh, hm(0), hm(1), hm(2), G, F);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] += F[v];
+        } else {
+          R h[3];
+#pragma unroll
+          for (int d = 0; d < 3; ++d) h[d] = half_metric([&](int m) { return sM[L::f(d, w, sc + m, NN)]; });
+          const NodeSpace<R> B = node_space(qa, h[0], h[1], h[2], G);
+          R D[5][5];  // projected first differences of Q along n-2 .. n+3
+#pragma unroll
+          for (int tt = 0; tt < 5; ++tt) {
+            R t[5];
+#pragma unroll
+            for (int v = 0; v < 5; ++v) t[v] = sFn[L::f(v, w, s + tt + 1, NN)] - sFn[L::f(v, w, s + tt, NN)];
+            project_diff(B, t, D[tt]);
+          }
+          R vl[5], vr[5], q[5], u[5], F[5];
+          const R eps4 = R(4) * eps;
+#pragma unroll
+          for (int f = 0; f < 5; ++f) {
+            vl[f] = weno_left_diff(D[0][f], D[1][f], D[2][f], D[3][f], eps4, linear);
+            vr[f] = weno_left_diff(-D[4][f], -D[3][f], -D[2][f], -D[1][f], eps4, linear);
+          }
+          const R hh = h[0] * h[0] + h[1] * h[1] + h[2] * h[2];
+          const R minv = rsq(hh), mag = hh * minv;
+#pragma unroll
+          for (int v = 0; v < 5; ++v) q[v] = sFn[L::f(v, w, sc, NN)];
+          unproject_diff(B, G, vl, q, u);
+          state_flux<+1>(u, G, h[0], h[1], h[2], mag, minv, F);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] = F[v];
+#pragma unroll
+          for (int v = 0; v < 5; ++v) q[v] = sFn[L::f(v, w, sc + 1, NN)];
+          unproject_diff(B, G, vr, q, u);
+          state_flux<-1>(u, G, h[0], h[1], h[2], mag, minv, F);
+#pragma unroll
+          for (int v = 0; v < 5; ++v) sF[L::f(v, w, s, NH)] += F[v];
+        }
       }
     }
     // a staged Q in FP64 is exact: the output node's copy for the RK combination is read
@@ -942,14 +1003,14 @@ __device__ __forceinline__ void sweep_tile(const SweepCommon& c, const SweepBloc
       if (c.do_inv && at0 >= 0 && at0 + 6 < nn) {
 #pragma unroll 1
         for (int m = 0; m < 7; ++m) {
-          const R wgt = R(os6_weight(row, sign, m));
+          const R wgt = os6_weight(os_tab, row, sign, m);
 #pragma unroll
           for (int v = 0; v < 4; ++v) acc[v] += wgt * sV[L::f(v, w, at0 + m, NN)];
         }
       } else {
 #pragma unroll 1
         for (int m = 0; m < 7; ++m) {
-          const R wgt = R(os6_weight(row, sign, m));
+          const R wgt = os6_weight(os_tab, row, sign, m);
 #pragma unroll
           for (int v = 0; v < 4; ++v)
             acc[v] += wgt * ldg(plane_ptr(vis, v * plane), po + (uint32_t)(first + m - d0 - s) * sd);
@@ -1166,10 +1227,17 @@ hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s) {
   const int64_t nwg = (int64_t)a.b.tiles_c1 * a.b.tiles_d * g.nk;
   if (nwg > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)nwg), wg(64);
-  if (a.b.one_sided & 3)
+  const bool os = a.b.one_sided & 3;
+  if (a.c.ph.scheme == kOriginal) {
+    if (os)
+      hipLaunchKernelGGL((k_sweep_w3<0, double, 1, kRowNodes, 64, true>), grid, wg, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_sweep_w3<0, double, 1, kRowNodes, 64, false>), grid, wg, 0, s, a);
+  } else if (os) {
     hipLaunchKernelGGL((k_sweep<0, double, 1, kRowNodes, 64, kModified, true>), grid, wg, 0, s, a);
-  else
+  } else {
     hipLaunchKernelGGL((k_sweep<0, double, 1, kRowNodes, 64, kModified, false>), grid, wg, 0, s, a);
+  }
   return hipGetLastError();
 }
 
@@ -1421,11 +1489,17 @@ template hipError_t launch_sweep_all_batch<float>(const SweepBlock*, const Sweep
 // flight and the node's basis do not fit less, and the SIMDs are 88-92% busy.
 // Measured, 512 x 512 x 384: zeta 4.47 -> 3.41 ms, eta 4.78 -> 3.71 ms (17.7 GB at 95% of the
 // rate of a device copy); 160^3 193 -> 153 us and 239 -> 168 us.
+//
+// The original scheme walks the same way with one slot more: node p completes the stencil
+// p-5 .. p of the half point p-5/2, whose flux goes to outputs p-3 and p-2 at once (160^3 eta
+// 242 -> 179 us, zeta 234 -> 172 us).  Outputs next to a face with the one-sided viscous
+// closure are left out of the scatter of viscous fluxes and take their seven-point sum when
+// they are stored (190 x 131 x 93 with walls in eta: 131 -> 117 us).
 // =====================================================================================
 constexpr int kMarchNT = 256;  // threads (grid lines) of a workgroup; two workgroups per CU
 constexpr int kMarchSlot = 8 * kMarchNT;  // LDS doubles of one node: Q (5) and the metric (3)
 
-template <int DIR, bool VIS, bool PREV>
+template <int DIR, int SCHEME, bool VIS, bool PREV, bool OS>
 __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlock& b, int grp, int chunk, int len,
                                             double* sh) {
   static_assert(DIR == 1 || DIR == 2, "lanes run along i");
@@ -1443,6 +1517,7 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
   const uint32_t base = (uint32_t)at(g, 0, 0, 0) + (uint32_t)(line % g.ni) + (uint32_t)(line / g.ni) * s2;
   const Gas<R> G(c.ph);
   const R eps4 = 4.0 * c.ph.eps;
+  const int faces = OS ? (b.one_sided >> (2 * DIR)) & 3 : 0;  // with the one-sided closure
 
   GP<const double> Q[5], V[4], I[5], M[3];
   GP<double> O[5];
@@ -1480,20 +1555,44 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
   auto put = [&](int o) {
     if (o >= o0 && o < o1 && act) {
       const uint32_t e = base + (uint32_t)o * sd;
+      if constexpr (OS && VIS) {
+        int first, row, sign;
+        if (one_sided_window(faces, o, nd, &first, &row, &sign)) {
+#pragma unroll
+          for (int v = 1; v < 5; ++v) {  // seven loads in flight
+            R y[7];
+#pragma unroll
+            for (int m = 0; m < 7; ++m) y[m] = ldg(V[v - 1], base + (uint32_t)(first + m) * sd);
+#pragma unroll
+            for (int m = 0; m < 7; ++m) done[v] += os6_weight(row, sign, m) * y[m];
+          }
+        }
+      }
 #pragma unroll
       for (int v = 0; v < 5; ++v) stg(O[v], e, PREV ? done[v] + rr[v] : done[v]);
     }
   };
-  // F+ of the node before at its n+1/2, and the metric of that half point
+  // modified scheme: F+ of the node before at its n+1/2, and the metric of that half point
   double* const SF = sh + 4 * kMarchSlot + threadIdx.x;
+  if constexpr (SCHEME == kModified) {
 #pragma unroll
-  for (int v = 0; v < 8; ++v) SF[v * NT] = 1.0;
+    for (int v = 0; v < 8; ++v) SF[v * NT] = 1.0;
+  }
   R mag = 1.0, minv = 1.0;
   R mc[3];  // metric of node p
 
-  // one node; S0 .. S3 are the slots of nodes p-4 .. p-1, and S0 takes node p
-  auto step = [&](int p, R(*A)[5], const Operands& x, Operands& next, double* S0, const double* S1, const double* S2,
-                  const double* S3) {
+  // one node; S[0] .. are the slots of the nodes before it (p-4 .. p-1, original scheme p-5 ..
+  // p-1) starting with slot k, the oldest, which takes node p
+  constexpr int SLOTS = SCHEME == kModified ? 4 : 5;
+  double* S[SLOTS];
+#pragma unroll
+  for (int n = 0; n < SLOTS; ++n) S[n] = sh + n * kMarchSlot + threadIdx.x;
+  auto step = [&](int p, R(*A)[5], const Operands& x, Operands& next, int k) {
+    auto slot = [&](int n) { return S[(n + k) % SLOTS]; };
+    double* const S0 = slot(0);
+    const double* const S1 = slot(1);
+    const double* const S2 = slot(2);
+    const double* const S3 = slot(3);
     load(next, p + 1);
     __builtin_amdgcn_sched_barrier(0);  // phase borders: the scheduler would overlap phases into spills
     R F[5];
@@ -1507,20 +1606,27 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
       A[5][v] -= R(13.0 / 320.0) * F[v];
       A[6][v] = R(19.0 / 3840.0) * F[v];
     }
-    if constexpr (VIS) {
+    if constexpr (VIS) {  // d6 of the viscous flux; outputs next to a one-sided face take theirs in put
+      auto add = [&](auto central) {
 #pragma unroll
-      for (int v = 1; v < 5; ++v) {  // d6 of the viscous flux
-        A[0][v] += R(1.0 / 60.0) * x.v[v - 1];
-        A[1][v] -= R(0.15) * x.v[v - 1];
-        A[2][v] += R(0.75) * x.v[v - 1];
-        A[4][v] -= R(0.75) * x.v[v - 1];
-        A[5][v] += R(0.15) * x.v[v - 1];
-        A[6][v] -= R(1.0 / 60.0) * x.v[v - 1];
-      }
+        for (int v = 1; v < 5; ++v) {
+          const R y = x.v[v - 1];
+          if (central(p - 3)) A[0][v] += R(1.0 / 60.0) * y;
+          if (central(p - 2)) A[1][v] -= R(0.15) * y;
+          if (central(p - 1)) A[2][v] += R(0.75) * y;
+          if (central(p + 1)) A[4][v] -= R(0.75) * y;
+          if (central(p + 2)) A[5][v] += R(0.15) * y;
+          if (central(p + 3)) A[6][v] -= R(1.0 / 60.0) * y;
+        }
+      };
+      if (OS && (((faces & 1) && p < 6) || ((faces & 2) && p > nd - 7)))
+        add([&](int o) { return !(((faces & 1) && o < 3) || ((faces & 2) && o > nd - 4)); });
+      else
+        add([](int) { return true; });
     }
     __builtin_amdgcn_sched_barrier(0);
     put(p - 4);
-    if (p > o0) {  // node n = p-2, from n = o0-1 on
+    if (SCHEME == kModified && p > o0) {  // node n = p-2, from n = o0-1 on
       R qn[5], mn[3], h[3];
 #pragma unroll
       for (int v = 0; v < 5; ++v) qn[v] = S2[v * NT];
@@ -1577,6 +1683,63 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
       for (int v = 0; v < 5; ++v) SF[v * NT] = F[v];
 #pragma unroll
       for (int v = 0; v < 3; ++v) SF[(5 + v) * NT] = h[v];
+    } else if (SCHEME == kOriginal && p > o0 + 1) {  // half point n+1/2, n = p-3, from n = o0-1 on
+      const double* const S4 = slot(SLOTS - 1);
+      R h[3], qa[5];
+#pragma unroll
+      for (int v = 0; v < 3; ++v)
+        h[v] = R(3.0 / 256.0) * (S0[(5 + v) * NT] + mc[v]) - R(25.0 / 256.0) * (S1[(5 + v) * NT] + S4[(5 + v) * NT]) +
+               R(150.0 / 256.0) * (S2[(5 + v) * NT] + S3[(5 + v) * NT]);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) qa[v] = R(0.5) * (S2[v * NT] + S3[v * NT]);
+      const NodeSpace<R> B = node_space(qa, h[0], h[1], h[2], G);
+      R D[5][5];  // projected first differences of Q along p-5 .. p
+      {
+        const double* const line[5] = {S0, S1, S2, S3, S4};
+        R t[5];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v) t[v] = line[n + 1][v * NT] - line[n][v * NT];
+          project_diff(B, t, D[n]);
+        }
+#pragma unroll
+        for (int v = 0; v < 5; ++v) t[v] = x.q[v] - S4[v * NT], S0[v * NT] = x.q[v];
+#pragma unroll
+        for (int v = 0; v < 3; ++v) S0[(5 + v) * NT] = mc[v];
+        project_diff(B, t, D[4]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      R vl[5], vr[5];
+#pragma unroll
+      for (int f = 0; f < 5; ++f) {
+        vl[f] = weno_left_diff<R>(D[0][f], D[1][f], D[2][f], D[3][f], eps4, false);
+        vr[f] = weno_left_diff<R>(-D[4][f], -D[3][f], -D[2][f], -D[1][f], eps4, false);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (PREV) {
+        const uint32_t e = base + (uint32_t)max(p - 3, 0) * sd;
+#pragma unroll
+        for (int v = 0; v < 5; ++v) rr[v] = ldg(I[v], e);
+      }
+      const R m2 = h[0] * h[0] + h[1] * h[1] + h[2] * h[2];
+      minv = rsq(m2);
+      mag = m2 * minv;
+      R q[5], u[5], Fm[5];
+#pragma unroll
+      for (int v = 0; v < 5; ++v) q[v] = S2[v * NT];
+      unproject_diff(B, G, vl, q, u);
+      state_flux<+1>(u, G, h[0], h[1], h[2], mag, minv, F);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) q[v] = S3[v * NT];
+      unproject_diff(B, G, vr, q, u);
+      state_flux<-1>(u, G, h[0], h[1], h[2], mag, minv, Fm);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        const R f = F[v] + Fm[v];
+        A[0][v] -= f;
+        A[1][v] += f;
+      }
     } else {
 #pragma unroll
       for (int v = 0; v < 5; ++v) S0[v * NT] = x.q[v];
@@ -1590,9 +1753,6 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
     for (int v = 0; v < 3; ++v) mc[v] = x.m[v];
   };
 
-  double* S[4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n) S[n] = sh + n * kMarchSlot + threadIdx.x;
   int p = o0 - 3;
 #pragma unroll
   for (int v = 0; v < 3; ++v) mc[v] = ldg(M[v], base + (uint32_t)p * sd);
@@ -1601,14 +1761,13 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
   // output o is final after step o+3; the last step may be one past the chunk
 #pragma unroll 1
   for (; p < o1 + 3; p += 2) {
-    step(p, A, even, odd, S[0], S[1], S[2], S[3]);
-    step(p + 1, A + 1, odd, even, S[1], S[2], S[3], S[0]);
-    double* t = S[0];
-    S[0] = S[2];
-    S[2] = t;
-    t = S[1];
-    S[1] = S[3];
-    S[3] = t;
+    step(p, A, even, odd, 0);
+    step(p + 1, A + 1, odd, even, 1);
+    double* old[SLOTS];
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n) old[n] = S[n];
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n) S[n] = old[(n + 2) % SLOTS];
 #pragma unroll
     for (int o = 0; o < 6; ++o)
 #pragma unroll
@@ -1617,12 +1776,12 @@ __device__ __forceinline__ void march_lines(const SweepCommon& c, const SweepBlo
   if (p == o1 + 3) put(o1 - 1);  // no step past the chunk stored it
 }
 
-template <int DIR, bool VIS, bool PREV>
+template <int DIR, int SCHEME, bool VIS, bool PREV, bool OS>
 __global__ __launch_bounds__(kMarchNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_march(SweepArgs a, int groups,
                                                                                               int len) {
   __shared__ double sh[5 * kMarchSlot];
   const int t = xcd_remap(blockIdx.x, gridDim.x);
-  march_lines<DIR, VIS, PREV>(a.c, a.b, t % groups, t / groups, len, sh);
+  march_lines<DIR, SCHEME, VIS, PREV, OS>(a.c, a.b, t % groups, t / groups, len, sh);
 }
 
 // Chunk length of the marching sweep, or 0 where the tiles are faster.  A workgroup puts one
@@ -1651,31 +1810,39 @@ static int march_len(int dir, const Geom& g) {
   return best_len;
 }
 
-template <int DIR>
+template <int DIR, int SCHEME, bool OS>
 static void launch_march_dir(const SweepArgs& a, int groups, int chunks, int len, hipStream_t s) {
   const dim3 grid(groups * chunks), wg(kMarchNT);
   if (a.c.do_vis && a.c.has_prev)
-    hipLaunchKernelGGL((k_march<DIR, true, true>), grid, wg, 0, s, a, groups, len);
+    hipLaunchKernelGGL((k_march<DIR, SCHEME, true, true, OS>), grid, wg, 0, s, a, groups, len);
   else if (a.c.do_vis)
-    hipLaunchKernelGGL((k_march<DIR, true, false>), grid, wg, 0, s, a, groups, len);
+    hipLaunchKernelGGL((k_march<DIR, SCHEME, true, false, OS>), grid, wg, 0, s, a, groups, len);
   else if (a.c.has_prev)
-    hipLaunchKernelGGL((k_march<DIR, false, true>), grid, wg, 0, s, a, groups, len);
+    hipLaunchKernelGGL((k_march<DIR, SCHEME, false, true, false>), grid, wg, 0, s, a, groups, len);
   else
-    hipLaunchKernelGGL((k_march<DIR, false, false>), grid, wg, 0, s, a, groups, len);
+    hipLaunchKernelGGL((k_march<DIR, SCHEME, false, false, false>), grid, wg, 0, s, a, groups, len);
+}
+template <int DIR>
+static void launch_march_scheme(const SweepArgs& a, int groups, int chunks, int len, hipStream_t s) {
+  const bool os = (a.b.one_sided >> (2 * DIR)) & 3;
+  if (a.c.ph.scheme == kOriginal)
+    os ? launch_march_dir<DIR, kOriginal, true>(a, groups, chunks, len, s)
+       : launch_march_dir<DIR, kOriginal, false>(a, groups, chunks, len, s);
+  else
+    os ? launch_march_dir<DIR, kModified, true>(a, groups, chunks, len, s)
+       : launch_march_dir<DIR, kModified, false>(a, groups, chunks, len, s);
 }
 
 bool launch_march(int dir, const SweepArgs& a, hipStream_t s, hipError_t* err) {
-  const bool os = (a.b.one_sided >> (2 * dir)) & 3;
-  if (dir == 0 || a.c.out_kind != kOutPartial || !a.c.do_inv || a.c.ph.linear || a.c.ph.scheme != kModified || os)
-    return false;
+  if (dir == 0 || a.c.out_kind != kOutPartial || !a.c.do_inv || a.c.ph.linear) return false;
   const int len = march_len(dir, a.b.g);
   if (!len) return false;
   const int nd = dir == 1 ? a.b.g.nj : a.b.g.nk, n2 = dir == 1 ? a.b.g.nk : a.b.g.nj;
   const int groups = (int)(((int64_t)a.b.g.ni * n2 + kMarchNT - 1) / kMarchNT), chunks = (nd + len - 1) / len;
   if (dir == 1)
-    launch_march_dir<1>(a, groups, chunks, len, s);
+    launch_march_scheme<1>(a, groups, chunks, len, s);
   else
-    launch_march_dir<2>(a, groups, chunks, len, s);
+    launch_march_scheme<2>(a, groups, chunks, len, s);
   *err = hipGetLastError();
   return true;
 }

@@ -124,7 +124,7 @@ template <typename R>
 hipError_t launch_sweep_all_batch(const SweepBlock* blocks, const SweepCommon& c, const TileList tl[3], int max_points,
                                   hipStream_t s);
 
-// FP64 xi sweep of the modified scheme, one wave per line
+// FP64 xi sweep, one wave per line
 hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s);
 
 // FP64 eta or zeta sweep into partial sums by lines (JS weights, modified scheme, no one-sided

@@ -12,9 +12,11 @@ uniform stream leaves is all rounding: its root mean square is at most 1.25 of t
 import numpy as np
 import pytest
 
+import oracle as O
 from paper_2006_07964_amd import binding as B
 from paper_2006_07964_amd import workloads as W
 from tests._gpu import DevBlock, normwise
+from tests.test_closure_gpu import axis_channel
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +52,30 @@ def test_march_agrees_with_tiles(size, mask):
     print(size, mask, err, free, free_tiles)
     assert np.all(err < 1e-12), err
     assert free <= 1.25 * free_tiles
+
+
+@pytest.mark.parametrize("case", ["original", "original Euler", "one-sided j walls", "one-sided k walls",
+                                  "one-sided j walls, original"])
+def test_march_of_other_forms_agrees_with_tiles(case):
+    """The original scheme, and the one-sided closure at walls across the marched direction
+    (chunks that start or end at a wall, and lines whose both ends are walls)."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    scheme = B.CFD_AFWENO_ORIGINAL if "original" in case else B.CFD_AFWENO_MODIFIED
+    if "one-sided" in case:
+        wl = axis_channel(1, shape=(163, 137, 97)) if "j walls" in case else axis_channel(2, shape=(131, 127, 139))
+        c = O.cfg_from_workload(wl)
+        q = O.bc_fill(c, O.periodic_wrap(c, O.wall_reset(c, wl.blocks[0].q)))
+    else:
+        wl, q = W.vortex_wavy(129, nj=131, nk=127), None
+    dev = DevBlock(wl, q=q, scheme=scheme)
+    try:
+        mask = ALL_INV if "Euler" in case else B.CFD_ALL
+        got = dev.rhs(mask).copy()
+        B.cfd_block_set_tiles(dev.h, B.cfd_block_tiles(dev.h))
+        err = normwise(got, dev.rhs(mask))
+    finally:
+        dev.close()
+    print(case, err)
+    assert np.all(err < 1e-12), err
