@@ -130,11 +130,12 @@ constexpr int kViscChunk = 128;  // most planes per workgroup (fewer when nk is 
 // Two tile shapes.  64 x 16 columns (1024 threads, one workgroup per CU) read the fewest halo
 // nodes of Q per output and stream a large block at the copy rate; 32 x 8 (256 threads, four
 // workgroups per CU) suit blocks whose Q stays in the 256 MB last-level cache, where the wider
-// halo costs little and finer, independently waiting workgroups fill the chip.  FP64 prepass,
-// 64 x 16 against 32 x 8, each at its best chunk: 32^3 11.1 / 7.4 us, 96x80x72 33.9 / 28.7,
-// 160^3 189 / 172, 192x112x72 74 / 68, 190x131x93 114 / 112, 256^3 755 / 793; FP32: 32^3
-// 8.9 / 7.5, 96x80x72 22.3 / 21.2, 160^3 130 / 124, 192x112x72 50.6 / 51.4, 190x131x93
-// 76 / 83, 256^3 521 / 596.  The lines lie between: 6M points in FP64, 1M in FP32.
+// halo costs little and finer, independently waiting workgroups fill the chip and leave less
+// of it idle in the last round.  FP64 prepass, 64 x 16 against 32 x 8, each at its best chunk:
+// 32^3 11.1 / 7.4 us, 101x94x99 54.2 / 55.5, 96x100x98 56.3 / 47.7, 130x96x120 95 / 89, 160^3
+// 189 / 172, 190x131x93 113 / 113, 186x150x181 227 / 240, 201x187x168 314 / 298, 256^3
+// 755 / 793; FP32: 32^3 8.9 / 7.5, 101x94x99 39.1 / 45.0, 96x100x98 37.0 / 36.8, 160^3
+// 130 / 124, 190x131x93 76 / 84, 201x187x168 200 / 221, 256^3 521 / 596.
 template <bool SMALL>
 struct ViscTile {
   static constexpr int VI = SMALL ? 32 : 64, VJ = SMALL ? 8 : 16, NT = VI * VJ;
@@ -143,7 +144,11 @@ struct ViscTile {
   static constexpr int SLOTS = SMALL ? 1024 : 256;  // workgroups the chip holds at once
   static_assert(NHALO <= NT, "one halo node per thread");
 };
-constexpr int64_t kViscSmallFp64 = 6000000, kViscSmallFp32 = 1000000;
+// At most kViscLatency points: 32 x 8, a round of a few planes whose latencies count.  Above,
+// the shape with the fewer rounds x planes (visc_plan), a plane of 32 x 8 taking 8% (FP64) or
+// 24% (FP32) longer; from kViscTraffic points on the halo traffic reaches memory: 64 x 16.
+constexpr int64_t kViscLatency = 600000, kViscTraffic = 7000000;
+constexpr double kViscSmallPlane[2] = {1.08, 1.24};  // FP64, FP32
 
 template <typename R, bool SMALL>
 struct ViscShared {
@@ -436,13 +441,25 @@ static int visc_cols(const Geom& g, bool small) {
 }
 
 // Tile shape, chunk lengths and tile counts of a launch over nb blocks (i-tile fastest, then
-// j-tile, then k-chunk).  One block, or a batch of blocks that take the small shape: the chunk
-// bound c (<= kViscChunk) with the least rounds x (c + 3), rounds the times the tiles fill the
-// chip and 3 the measured cost of the six priming planes of a chunk in units of an output
-// plane; nk is then split into the fewest equal chunks under c.  (160^3 FP64 before, with a
-// bound halved until 256 tiles were reached: 300 tiles of 1024 threads, two rounds, 258 us.)
-// A batch of large blocks has several rounds in any case and keeps chunks of at most
-// kViscChunk, halved (down to 8) where a block has fewer than kViscMinTilesBatch tiles.
+// j-tile, then k-chunk).  For a shape, the chunk bound c (<= kViscChunk) with the least rounds
+// x (c + 3), rounds the times the tiles fill the chip and 3 the measured cost of the six
+// priming planes of a chunk in units of an output plane; nk is then split into the fewest
+// equal chunks under c.  (160^3 FP64 before, with a bound halved until 256 tiles were reached:
+// 300 tiles of 1024 threads, two rounds, 258 us.)  A batch of kViscTraffic points or more has
+// several rounds in any case and keeps chunks of at most kViscChunk, halved (down to 8) where
+// a block has fewer than kViscMinTilesBatch tiles.
+static int64_t visc_chunk(const Geom* gs, int nb, int nkmax, bool small, int* chunk) {
+  const int slots = small ? ViscTile<true>::SLOTS : ViscTile<false>::SLOTS;
+  int64_t best = INT64_MAX;
+  for (int c = nkmax < kViscChunk ? nkmax : kViscChunk; c >= 1; --c) {
+    int64_t t = 0;
+    for (int b = 0; b < nb; ++b) t += (int64_t)visc_cols(gs[b], small) * ((gs[b].nk + c - 1) / c);
+    const int64_t cost = ((t + slots - 1) / slots) * (c + 3);
+    if (cost < best) best = cost, *chunk = c;
+  }
+  return best;
+}
+
 void visc_plan(const Geom* gs, int nb, bool batch, bool fp64, bool* small_out, int* kc, int* tiles) {
   int64_t points = 0;
   int nkmax = 0;
@@ -450,23 +467,18 @@ void visc_plan(const Geom* gs, int nb, bool batch, bool fp64, bool* small_out, i
     points += (int64_t)gs[b].ni * gs[b].nj * gs[b].nk;
     nkmax = gs[b].nk > nkmax ? gs[b].nk : nkmax;
   }
-  const bool small = points < (fp64 ? kViscSmallFp64 : kViscSmallFp32);
-  *small_out = small;
-  int best = 0;
-  if (!batch || small) {
-    const int slots = small ? ViscTile<true>::SLOTS : ViscTile<false>::SLOTS;
-    int64_t best_cost = INT64_MAX;
-    for (int c = nkmax < kViscChunk ? nkmax : kViscChunk; c >= 1; --c) {
-      int64_t t = 0;
-      for (int b = 0; b < nb; ++b) t += (int64_t)visc_cols(gs[b], small) * ((gs[b].nk + c - 1) / c);
-      const int64_t cost = ((t + slots - 1) / slots) * (c + 3);
-      if (cost < best_cost) best_cost = cost, best = c;
-    }
+  int chunk[2] = {0, 0};  // 64 x 16, 32 x 8
+  bool small = points <= kViscLatency;
+  const int64_t small_cost = visc_chunk(gs, nb, nkmax, true, &chunk[1]);
+  if (!small) {
+    const int64_t large_cost = visc_chunk(gs, nb, nkmax, false, &chunk[0]);
+    small = points < kViscTraffic && kViscSmallPlane[fp64 ? 0 : 1] * small_cost < large_cost;
   }
+  *small_out = small;
   for (int b = 0; b < nb; ++b) {
     const int cols = visc_cols(gs[b], small), nk = gs[b].nk;
-    int c = best;
-    if (!c)
+    int c = chunk[small ? 1 : 0];
+    if (batch && points >= kViscTraffic)
       for (c = kViscChunk; c > 8 && cols * ((nk + c - 1) / c) < kViscMinTilesBatch;) c /= 2;
     const int nch = (nk + c - 1) / c;
     kc[b] = (nk + nch - 1) / nch;
@@ -1800,7 +1812,8 @@ static int march_len(int dir, const Geom& g) {
   double best = points / 47000.0;
   int best_len = 0;
   for (int chunks = 1; chunks <= nd; ++chunks) {
-    const int len = (nd + chunks - 1) / chunks;
+    int len = (nd + chunks - 1) / chunks;
+    len += len & 1;  // steps come in pairs
     const int64_t wgs = groups * ((nd + len - 1) / len);
     if (wgs > 16 * 1024 && chunks > 1) break;  // many rounds already
     const int64_t rounds = (wgs + 255) / 256;

@@ -25,7 +25,10 @@ VIS = 7 | B.CFD_TERM_VIS
     ((33, 7, 9), B.CFD_MIXED), ((65, 17, 61), B.CFD_MIXED),
     # just below and above the sizes at which the wide tile takes over
     ((189, 179, 177), B.CFD_FP64), ((190, 181, 177), B.CFD_FP64),
-    ((101, 100, 99), B.CFD_MIXED), ((101, 101, 99), B.CFD_MIXED)])
+    ((101, 100, 99), B.CFD_MIXED), ((101, 101, 99), B.CFD_MIXED),
+    # between: the shape with the cheaper rounds, the narrow tile's and the wide tile's
+    ((96, 100, 98), B.CFD_FP64), ((101, 94, 99), B.CFD_FP64),
+    ((96, 100, 98), B.CFD_MIXED), ((101, 94, 99), B.CFD_MIXED)])
 def test_viscous_rhs_at_tile_edges(size, precision):
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
