@@ -127,6 +127,12 @@ constexpr int kDefaultTiles[2][3] = {{5, 6, 6}, {5, 2, 0}};
 // 254 / 252, 80^3 358 / 376 (the three sets of partial sums are extra traffic); mixed 48^3
 // 115 / 101, 80^3 273 / 267, 96x80x72 281 / 276, 96^3 410 / 423
 constexpr int64_t kAllPoints[2] = {300000, 600000};
+// largest block, or batch in all, whose viscous prepass runs in that launch too.  RK3 step,
+// prepass before / within: FP64 32^3 74 / 70 us, 48^3 124 / 123, 52x50x52 145 / 148, 64^3
+// 225 / 228 (the sum then gathers 72 flux values per node); mixed 48^3 99 / 92, 64^3 169 / 155,
+// 80^3 272 / 273.  Batches: FP64 8 blocks of 10k points in all 125 / 114, 6 of 97k 208 / 200,
+// 24 of 118k 241 / 248; mixed 8 of 10k 117 / 108, 12 of 184k 238 / 225
+constexpr int64_t kFusedPoints[2] = {110000, 600000};
 
 struct cfd_block {
   cfd_block_desc d;
@@ -147,9 +153,7 @@ struct cfd_block {
   size_t esize = 8;       // bytes of the compute type
   bool have_metrics = false;
   int64_t bytes = 0;
-  // block-local viscous halo work: self-periodic copies and physical-face ghosts
-  CopySeg* local_copy_dev = nullptr;
-  int n_local_copy = 0, max_local_copy = 0;
+  // viscous ghosts of the physical faces
   BcSeg* local_bc_dev = nullptr;
   int n_local_bc = 0, max_local_bc = 0;
   bool has_interface = false;
@@ -422,8 +426,7 @@ int one_sided_mask(const cfd_block_desc& d) {
   return m;
 }
 
-// viscous fluxes of one block with block-local halos (periodic wraps, physical ghosts)
-int run_visc(cfd_block* b, const double* Q) {
+ViscArgs visc_args(const cfd_block* b, const double* Q) {
   ViscArgs va;
   std::memset(&va, 0, sizeof va);
   va.g = b->g;
@@ -433,28 +436,30 @@ int run_visc(cfd_block* b, const double* Q) {
   va.vis = b->vis;
   va.ph = make_phys(b->d.params);
   va.one_sided = one_sided_mask(b->d);
-  // the prepass writes the periodic images itself (they were the only local copies)
+  // the prepass writes the periodic images itself
   for (int ax = 0; ax < 3; ++ax)
     if (b->d.bc[2 * ax] == CFD_BC_PERIODIC) va.periodic |= 1 << ax;
+  return va;
+}
+
+// viscous ghosts of a block's physical faces, after its fluxes
+int run_visc_ghosts(cfd_block* b) {
+  if (!b->n_local_bc) return CFD_OK;
+  PtrTable t = single_table<double>(b->vis, b->g.plane);
+  hipError_t e = b->d.precision == CFD_FP64
+                     ? launch_visc_ghost<double>(b->local_bc_dev, b->n_local_bc, b->max_local_bc, t, b->stream)
+                     : launch_visc_ghost<float>(b->local_bc_dev, b->n_local_bc, b->max_local_bc, t, b->stream);
+  return e == hipSuccess ? CFD_OK : hip_fail(e, "visc ghost fill");
+}
+
+// viscous fluxes of one block with block-local halos (periodic wraps, physical ghosts)
+int run_visc(cfd_block* b, const double* Q) {
+  const ViscArgs va = visc_args(b, Q);
   ProfScope ps(&b->prof, "visc_prepass", b->stream);
   hipError_t e = b->d.precision == CFD_FP64 ? launch_visc<double>(va, b->stream) : launch_visc<float>(va, b->stream);
   ps.done();
   if (e != hipSuccess) return hip_fail(e, "visc_prepass launch");
-  if (b->n_local_copy && !va.periodic) {
-    PtrTable t = single_table<double>(b->vis, b->g.plane);
-    ProfScope pc(&b->prof, "visc_halo", b->stream);
-    e = b->d.precision == CFD_FP64 ? launch_copy<double>(b->local_copy_dev, b->n_local_copy, b->max_local_copy, t, b->stream)
-                                   : launch_copy<float>(b->local_copy_dev, b->n_local_copy, b->max_local_copy, t, b->stream);
-    pc.done();
-    if (e != hipSuccess) return hip_fail(e, "visc halo copy");
-  }
-  if (b->n_local_bc) {
-    PtrTable t = single_table<double>(b->vis, b->g.plane);
-    e = b->d.precision == CFD_FP64 ? launch_visc_ghost<double>(b->local_bc_dev, b->n_local_bc, b->max_local_bc, t, b->stream)
-                                   : launch_visc_ghost<float>(b->local_bc_dev, b->n_local_bc, b->max_local_bc, t, b->stream);
-    if (e != hipSuccess) return hip_fail(e, "visc ghost fill");
-  }
-  return CFD_OK;
+  return run_visc_ghosts(b);
 }
 
 const char* kSweepNames[3] = {"sweep_xi", "sweep_eta", "sweep_zeta"};
@@ -464,8 +469,9 @@ const char* kProfNames[] = {"sweep_xi",    "sweep_eta",    "sweep_zeta",   "swee
                             "sweeps_rk"};
 
 // run the direction sweeps selected by mask; the last one writes R or the RK stage
+// (with_visc: and the viscous prepass before them)
 int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, double* out, const double* qn,
-               const double* dt_dev, double dt, double ca, double cb, double cc) {
+               const double* dt_dev, double dt, double ca, double cb, double cc, bool with_visc) {
   const bool inv = (mask & CFD_TERM_INV) != 0;
   const bool vis = (mask & CFD_TERM_VIS) != 0 && b->d.params.viscous;
   int dirs[3], nd = 0;
@@ -489,6 +495,11 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
   a.c.ca = ca;
   a.c.cb = cb;
   a.c.cc = cc;
+  const bool one_launch = nd == 3 && inv && b->all_sweeps && !b->own_tiles;  // takes the prepass itself
+  if (with_visc && vis && !one_launch) {
+    const int rc = run_visc(b, Q);
+    if (rc) return rc;
+  }
   if (nd == 0 || (!inv && !vis)) {
     // nothing to evaluate: R = 0 or Qout = ca Qn + cb Q, via a zero-term sweep along xi
     a.c.do_inv = 0;
@@ -502,13 +513,27 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     ps.done();
     return e == hipSuccess ? CFD_OK : hip_fail(e, "sweep launch");
   }
-  if (nd == 3 && inv && b->all_sweeps && !b->own_tiles) {
+  if (one_launch) {
     a.b.rt_in = b->rt;
     a.b.rt_out = b->rt;
     a.b.out = out;
     a.c.out_kind = out_kind;
+    const bool f64 = b->d.precision == CFD_FP64;
+    const bool fused = with_visc && vis && (int64_t)b->g.ni * b->g.nj * b->g.nk <= kFusedPoints[f64 ? 0 : 1];
+    if (with_visc && vis && !fused) {
+      const int rc = run_visc(b, Q);
+      if (rc) return rc;
+    }
+    const ViscArgs va = visc_args(b, Q);
     ProfScope ps(&b->prof, out_kind == kOutRK ? "sweeps_rk" : "sweeps", b->stream);
-    hipError_t e = b->d.precision == CFD_FP64 ? launch_sweep_all<double>(a, b->stream) : launch_sweep_all<float>(a, b->stream);
+    hipError_t e = f64 ? launch_sweep_all<double>(fused ? &va : nullptr, a, b->stream)
+                       : launch_sweep_all<float>(fused ? &va : nullptr, a, b->stream);
+    if (e == hipSuccess && fused) {
+      const int rc = run_visc_ghosts(b);
+      if (rc) return rc;
+    }
+    if (e == hipSuccess)
+      e = f64 ? launch_combine<double>(fused, a, b->stream) : launch_combine<float>(fused, a, b->stream);
     ps.done();
     return e == hipSuccess ? CFD_OK : hip_fail(e, "sweep launch");
   }
@@ -632,23 +657,14 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
   if (hipEventCreateWithFlags(&b->ev, hipEventDisableTiming) != hipSuccess) return cleanup(CFD_ERR_HIP, "block event");
   const int planes = (b->esize == sizeof(double) ? 17 : 36) + (b->all_sweeps ? 10 : 0);
   b->bytes = (int64_t)plane * (10 * 8 + planes * (int64_t)b->esize);
-  // block-local viscous halo work
-  std::vector<CopySeg> cs;
+  // viscous ghosts of the physical faces
   std::vector<BcSeg> bs;
-  for (int ax = 0; ax < 3; ++ax) {
-    if (d->bc[2 * ax] == CFD_BC_PERIODIC) {
-      cs.push_back(make_copy(b->g, 0, 2 * ax, b->g, 0, 2 * ax + 1, 4 * ax, 4));
-      cs.push_back(make_copy(b->g, 0, 2 * ax + 1, b->g, 0, 2 * ax, 4 * ax, 4));
-    }
-  }
   for (int f = 0; f < 6; ++f) {
     if (is_physical(d->bc[f])) bs.push_back(make_bc(b->g, 0, f, d->bc[f]));
     if (d->bc[f] == CFD_BC_INTERFACE) b->has_interface = true;
   }
-  for (auto& s : cs) b->max_local_copy = std::max(b->max_local_copy, s.na * s.nb * kHalo * s.nplanes);
   for (auto& s : bs) b->max_local_bc = std::max(b->max_local_bc, s.na * s.nb);
-  if (upload(cs, &b->local_copy_dev) || upload(bs, &b->local_bc_dev)) return cleanup(CFD_ERR_HIP, "halo tables");
-  b->n_local_copy = (int)cs.size();
+  if (upload(bs, &b->local_bc_dev)) return cleanup(CFD_ERR_HIP, "halo tables");
   b->n_local_bc = (int)bs.size();
   *out = b;
   return CFD_OK;
@@ -668,7 +684,6 @@ int cfd_block_destroy(cfd_block* b) {
   (void)hipFree(b->res_dev);
   if (b->pin) (void)hipHostFree(b->pin);
   if (b->ev) (void)hipEventDestroy(b->ev);
-  (void)hipFree(b->local_copy_dev);
   (void)hipFree(b->local_bc_dev);
   delete b;
   return CFD_OK;
@@ -735,30 +750,29 @@ int cfd_rhs_sweeps(cfd_block* b, const double* Q, double* R, unsigned mask) {
   if (!b || !Q || !R) return fail(CFD_ERR_ARG, "null argument");
   if (Q == R) return fail(CFD_ERR_ARG, "R must not alias Q");
   if (!b->have_metrics) return fail(CFD_ERR_STATE, "cfd_metrics has not been run on this block");
-  return run_sweeps(b, Q, mask, kOutRhs, R, nullptr, nullptr, 0.0, 0.0, 0.0, 0.0);
+  return run_sweeps(b, Q, mask, kOutRhs, R, nullptr, nullptr, 0.0, 0.0, 0.0, 0.0, false);
 }
 
 int cfd_rhs(cfd_block* b, const double* Q, double* R, unsigned mask) {
   if (!b || !Q || !R) return fail(CFD_ERR_ARG, "null argument");
   if (b->has_interface || b->patched)
     return fail(CFD_ERR_STATE, "block has interface faces: use cfd_viscous_fluxes, cfd_halo_exchange(VISC), cfd_rhs_sweeps");
-  if ((mask & CFD_TERM_VIS) && b->d.params.viscous) {
-    int rc = cfd_viscous_fluxes(b, Q);
-    if (rc) return rc;
-  }
-  return cfd_rhs_sweeps(b, Q, R, mask);
+  if (Q == R) return fail(CFD_ERR_ARG, "R must not alias Q");
+  if (!b->have_metrics) return fail(CFD_ERR_STATE, "cfd_metrics has not been run on this block");
+  return run_sweeps(b, Q, mask, kOutRhs, R, nullptr, nullptr, 0.0, 0.0, 0.0, 0.0, true);
 }
 
 static int rk_sweeps(cfd_block* b, int stage, const double* dt_dev, double dt, const double* Qn, const double* Qcur,
-                     double* Qout) {
+                     double* Qout, bool with_visc) {
   int rc = check_rk_args(b, stage, Qn, Qcur, Qout);
   if (rc) return rc;
-  return run_sweeps(b, Qcur, CFD_ALL, kOutRK, Qout, Qn, dt_dev, dt, kRK[stage][0], kRK[stage][1], kRK[stage][2]);
+  return run_sweeps(b, Qcur, CFD_ALL, kOutRK, Qout, Qn, dt_dev, dt, kRK[stage][0], kRK[stage][1], kRK[stage][2],
+                    with_visc);
 }
 
 int cfd_rk_sweeps(cfd_block* b, int stage, double dt, const double* Qn, const double* Qcur, double* Qout) {
   if (!std::isfinite(dt)) return fail(CFD_ERR_ARG, "dt must be finite");
-  return rk_sweeps(b, stage, nullptr, dt, Qn, Qcur, Qout);
+  return rk_sweeps(b, stage, nullptr, dt, Qn, Qcur, Qout, false);
 }
 
 int cfd_rk_stage(cfd_block* b, int stage, double dt, const double* Qn, const double* Qcur, double* Qout) {
@@ -767,11 +781,7 @@ int cfd_rk_stage(cfd_block* b, int stage, double dt, const double* Qn, const dou
   if (!std::isfinite(dt)) return fail(CFD_ERR_ARG, "dt must be finite");
   if (b->has_interface || b->patched)
     return fail(CFD_ERR_STATE, "block has interface faces: use cfd_viscous_fluxes, cfd_halo_exchange(VISC), cfd_rk_sweeps");
-  if (b->d.params.viscous) {
-    rc = run_visc(b, Qcur);
-    if (rc) return rc;
-  }
-  return rk_sweeps(b, stage, nullptr, dt, Qn, Qcur, Qout);
+  return rk_sweeps(b, stage, nullptr, dt, Qn, Qcur, Qout, true);
 }
 
 int cfd_rk_stage_dev(cfd_block* b, int stage, const double* dt_dev, const double* Qn, const double* Qcur,
@@ -781,11 +791,7 @@ int cfd_rk_stage_dev(cfd_block* b, int stage, const double* dt_dev, const double
   if (!dt_dev) return fail(CFD_ERR_ARG, "null dt_dev");
   if (b->has_interface || b->patched)
     return fail(CFD_ERR_STATE, "block has interface faces: use cfd_viscous_fluxes, cfd_halo_exchange(VISC), cfd_rk_sweeps");
-  if (b->d.params.viscous) {
-    rc = run_visc(b, Qcur);
-    if (rc) return rc;
-  }
-  return rk_sweeps(b, stage, dt_dev, 0.0, Qn, Qcur, Qout);
+  return rk_sweeps(b, stage, dt_dev, 0.0, Qn, Qcur, Qout, true);
 }
 
 int cfd_sync(cfd_block* b) {
@@ -1217,25 +1223,43 @@ hipError_t launch_batch_sweep(cfd_batch* bt, int st, int d) {
              : launch_sweep_batch<float>(d, bt->cfg[d], bt->persist[d] != 0, a, c, tl, nwg, bt->stream);
 }
 
-// the three sweeps of a stage in one launch, then their sum
-hipError_t launch_batch_all(cfd_batch* bt, int st) {
+// the three sweeps of a stage in one launch (with_visc: and the viscous prepass)
+hipError_t launch_batch_all(cfd_batch* bt, int st, bool with_visc) {
+  const int nb = (int)bt->blocks.size();
+  const ViscArgs* va = with_visc ? bt->visc_args_dev + st * nb : nullptr;
+  const SweepBlock* a = bt->sweep_args_dev + st * 3 * nb;
+  const SweepCommon& c = bt->sweep_common[st][kSweepOrder[2]];
+  return bt->precision == CFD_FP64
+             ? launch_sweep_all_batch<double>(va, &bt->visc_tl, a, c, bt->sweep_tl, bt->stream)
+             : launch_sweep_all_batch<float>(va, &bt->visc_tl, a, c, bt->sweep_tl, bt->stream);
+}
+// and the launch that adds them
+hipError_t launch_batch_combine(cfd_batch* bt, int st, bool with_visc) {
   const int nb = (int)bt->blocks.size();
   int most = 0;
   for (const cfd_block* B : bt->blocks) most = std::max(most, B->g.ni * B->g.nj * B->g.nk);
   const SweepBlock* a = bt->sweep_args_dev + st * 3 * nb;
   const SweepCommon& c = bt->sweep_common[st][kSweepOrder[2]];
-  return bt->precision == CFD_FP64 ? launch_sweep_all_batch<double>(a, c, bt->sweep_tl, most, bt->stream)
-                                   : launch_sweep_all_batch<float>(a, c, bt->sweep_tl, most, bt->stream);
+  return bt->precision == CFD_FP64 ? launch_combine_batch<double>(with_visc, a, c, nb, most, bt->stream)
+                                   : launch_combine_batch<float>(with_visc, a, c, nb, most, bt->stream);
 }
 
 // one RK stage of every block (all launches on bt->stream)
 hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
   const int nb = (int)bt->blocks.size();
   hipError_t e = hipSuccess;
+  int64_t points = 0;
+  for (const cfd_block* B : bt->blocks) points += (int64_t)B->g.ni * B->g.nj * B->g.nk;
+  const bool fused =
+      bt->all_sweeps && bt->viscous && bt->visc_small && points <= kFusedPoints[bt->precision == CFD_FP64 ? 0 : 1];
   if (bt->viscous) {
     const ViscArgs* va = bt->visc_args_dev + st * nb;
-    e = bt->precision == CFD_FP64 ? launch_visc_batch<double>(va, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream)
-                                  : launch_visc_batch<float>(va, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream);
+    if (fused)
+      e = launch_batch_all(bt, st, true);
+    else
+      e = bt->precision == CFD_FP64
+              ? launch_visc_batch<double>(va, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream)
+              : launch_visc_batch<float>(va, bt->visc_tl, bt->visc_small, bt->one_sided, bt->stream);
     if (e != hipSuccess) return e;
     PtrTable t;
     std::memset(&t, 0, sizeof t);
@@ -1248,10 +1272,12 @@ hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
             : launch_visc_halo<float>(bt->vcopy_dev, bt->nvcopy, bt->maxvcopy, bt->vbc_dev, bt->nvbc, bt->maxvbc, t, bt->stream);
     if (e != hipSuccess) return e;
   }
-  if (bt->all_sweeps)
-    e = launch_batch_all(bt, st);
-  else
+  if (bt->all_sweeps) {
+    if (!fused) e = launch_batch_all(bt, st, false);
+    if (e == hipSuccess) e = launch_batch_combine(bt, st, fused);
+  } else {
     for (int n = 0; n < 3 && e == hipSuccess; ++n) e = launch_batch_sweep(bt, st, kSweepOrder[n]);
+  }
   if (e != hipSuccess) return e;
   // Q halos of every block: wall reset, interface / periodic copies, ghost fills
   BcArgs ba;
@@ -1351,7 +1377,11 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
     fill_tiles(bt);
     rc = upload_args(bt, Qn, QA, QB, dt_dev);
     float total = 0.f;
-    if (rc == CFD_OK) total = timed([&]() { return launch_batch_all(bt, 0); });
+    if (rc == CFD_OK)
+      total = timed([&]() {
+        const hipError_t e = launch_batch_all(bt, 0, false);
+        return e == hipSuccess ? launch_batch_combine(bt, 0, false) : e;
+      });
     if (rc != CFD_OK || total >= direction_ms[0] + direction_ms[1] + direction_ms[2]) {
       bt->all_sweeps = false;
       for (int d = 0; d < 3; ++d) bt->cfg[d] = cfg[d], bt->persist[d] = persist[d];

@@ -283,6 +283,22 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
 #pragma unroll
       for (int n = 0; n < 4; ++n) sp[n][hj - j0 + 3][hi - i0 + 3] = ph4[n];
     }
+    // the metrics and the flux planes stream through (read or written once): streaming
+    // accesses leave L2 to the Q rows and columns that the neighbouring tiles read as
+    // their halo (measured on the 512 x 512 x 384 channel: 4% faster in FP64).  The small
+    // tile, whose chunks are a plane or a few, requests its metrics before the barrier (32^3
+    // FP64 9.9 -> 7.4 us); the closure's kernels have no registers left for that.
+    constexpr bool EARLY = SMALL && !OS;
+    R mh[3][3], J;
+    auto load_metrics = [&]() {
+      const uint32_t p = pc + (uint32_t)k * sk;
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) mh[d][c] = ldg_nt(plane_ptr(met, (3 * d + c) * plane), p);
+      J = ldg_nt(plane_ptr(met, 9 * plane), p);
+    };
+    if (EARLY && act) load_metrics();
     __syncthreads();
     if (act) {
       R gr[4][3];  // d(u, v, w, T)/d(xi, eta, zeta)
@@ -331,15 +347,7 @@ __device__ __forceinline__ void visc_tile(const ViscArgs& a, int t, ViscShared<R
           for (int n = 0; n < 4; ++n) gr[n][d] = acc[n];
         }
       }
-      // the metrics and the flux planes stream through (read or written once): streaming
-      // accesses leave L2 to the Q rows and columns that the neighbouring tiles read as
-      // their halo (measured on the 512 x 512 x 384 channel: 4% faster in FP64)
-      R mh[3][3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) mh[d][c] = ldg_nt(plane_ptr(met, (3 * d + c) * plane), p);
-      const R J = ldg_nt(plane_ptr(met, 9 * plane), p);
+      if constexpr (!EARLY) load_metrics();
       R dx[4][3];  // d(u, v, w, T)/d(x, y, z), Eq 21
 #pragma unroll
       for (int n = 0; n < 4; ++n)
@@ -1344,12 +1352,15 @@ template hipError_t launch_sweep_batch<float>(int, int, bool, const SweepBlock*,
                                               hipStream_t);
 
 // =====================================================================================
-// The three direction sweeps of small blocks in one launch.  Their partial sums are
-// independent, so one grid covers the tiles of zeta, then eta, then xi, each direction writing
-// its own five planes, and a second launch adds them in the order of the sequential sweeps and
-// writes R or the RK stage: two dependent launches instead of three, and three times the
-// workgroups at once for blocks that do not fill the chip.  A launch that waits for another
-// costs 3-4 us before its own work; a sweep of 32^3 takes 6-7 us with that.
+// Small blocks: the viscous prepass and the three direction sweeps in one launch.  The
+// inviscid partial sums are independent of each other and of the viscous fluxes, so one grid
+// covers the tiles of the prepass, then of zeta, eta and xi, each direction writing its own
+// five planes; a second launch adds the derivative of the viscous flux to each and then the
+// three, in the order of the sequential sweeps, and writes R or the RK stage.  Two dependent
+// launches instead of four, with all their workgroups at once for blocks that do not fill the
+// chip: a launch that waits for another costs 3-4 us before its own work, and a sweep of 32^3
+// takes 6-7 us with that.  Where the fluxes exist already (the split form), the sweeps take
+// them as usual (WITH_VISC false in both kernels).
 // =====================================================================================
 template <typename R>
 constexpr int kAllTW = sizeof(R) == 8 ? 8 : 16;  // eta and zeta tiles (configurations 6 and 2)
@@ -1359,48 +1370,65 @@ constexpr int kAllNT = 256;
 
 template <typename R>
 union AllShared {
+  ViscShared<R, true> visc;
   SweepShared<R, 4, 58> xi;  // configuration 5
   SweepShared<R, kAllTW<R>, kAllTS<R>> across;
 };
 
-// blocks.b[d]: arguments and tiling of direction d; zeta has tiles [0, nz), eta the next ne
-template <typename R>
-__global__ __launch_bounds__(kAllNT) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_all(SweepCommon c, AllBlocks a,
-                                                                                             int nz, int ne) {
+// a.b[d]: arguments and tiling of direction d; the prepass has tiles [0, nv), zeta the next nz,
+// eta the next ne
+template <typename R, bool WITH_VISC>
+__global__ __launch_bounds__(kAllNT) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_all(
+    ViscArgs va, SweepCommon c, AllBlocks a, int nv, int nz, int ne) {
   __shared__ AllShared<R> sh;
-  const int t = blockIdx.x;
+  int t = blockIdx.x;
+  if (WITH_VISC && t < nv) {
+    visc_tile<R, false, true>(va, xcd_remap(t, nv), sh.visc);
+    return;
+  }
+  t -= nv;
   if (t < nz)
     sweep_tile<2, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, a.b[2], xcd_remap(t, nz), sh.across);
   else if (t < nz + ne)
     sweep_tile<1, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, a.b[1], xcd_remap(t - nz, ne), sh.across);
   else
-    sweep_tile<0, R, 4, 58, kAllNT>(c, a.b[0], xcd_remap(t - nz - ne, gridDim.x - nz - ne), sh.xi);
+    sweep_tile<0, R, 4, 58, kAllNT>(c, a.b[0], xcd_remap(t - nz - ne, gridDim.x - nv - nz - ne), sh.xi);
 }
 
-// blocks + 2 * nblk .. of zeta, + nblk .. of eta, + 0 .. of xi
-template <typename R>
+// The same over every block of a batch: nb xi blocks, then nb eta, then nb zeta.
+struct AllLists {
+  TileList v, z, e, x;  // prepass, zeta, eta, xi
+};
+template <typename R, bool WITH_VISC>
 __global__ __launch_bounds__(kAllNT) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_all_batch(
-    const SweepBlock* __restrict__ blocks, SweepCommon c, TileList tx, TileList te, TileList tz) {
+    const ViscArgs* __restrict__ va, const SweepBlock* __restrict__ blocks, SweepCommon c, AllLists tl) {
   __shared__ AllShared<R> sh;
-  const int nb = tx.nblk, nz = tz.prefix[nb], ne = te.prefix[nb];
+  const int nb = tl.x.nblk, nv = WITH_VISC ? tl.v.prefix[nb] : 0, nz = tl.z.prefix[nb], ne = tl.e.prefix[nb];
   int t = blockIdx.x, blk = 0;
+  if (WITH_VISC && t < nv) {
+    while (t >= tl.v.prefix[blk + 1]) ++blk;
+    visc_tile<R, false, true>(va[blk], t - tl.v.prefix[blk], sh.visc);
+    return;
+  }
+  t -= nv;
   if (t < nz) {
-    while (t >= tz.prefix[blk + 1]) ++blk;
-    sweep_tile<2, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, blocks[2 * nb + blk], t - tz.prefix[blk], sh.across);
+    while (t >= tl.z.prefix[blk + 1]) ++blk;
+    sweep_tile<2, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, blocks[2 * nb + blk], t - tl.z.prefix[blk], sh.across);
   } else if (t < nz + ne) {
     t -= nz;
-    while (t >= te.prefix[blk + 1]) ++blk;
-    sweep_tile<1, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, blocks[nb + blk], t - te.prefix[blk], sh.across);
+    while (t >= tl.e.prefix[blk + 1]) ++blk;
+    sweep_tile<1, R, kAllTW<R>, kAllTS<R>, kAllNT>(c, blocks[nb + blk], t - tl.e.prefix[blk], sh.across);
   } else {
     t -= nz + ne;
-    while (t >= tx.prefix[blk + 1]) ++blk;
-    sweep_tile<0, R, 4, 58, kAllNT>(c, blocks[blk], t - tx.prefix[blk], sh.xi);
+    while (t >= tl.x.prefix[blk + 1]) ++blk;
+    sweep_tile<0, R, 4, 58, kAllNT>(c, blocks[blk], t - tl.x.prefix[blk], sh.xi);
   }
 }
 
 // R or the RK stage from the three partial sums (b: the xi block; rt: zeta's five planes, then
-// eta's, then xi's)
-template <typename R>
+// eta's, then xi's); WITH_VISC: those are inviscid and the derivatives of the viscous fluxes
+// are added here
+template <typename R, bool WITH_VISC>
 __device__ __forceinline__ void combine_block(const SweepCommon& c, const SweepBlock& b) {
   const Geom& g = b.g;
   const GP<const R> rt = (GP<const R>)to_global(static_cast<const R*>(b.rt_in));
@@ -1408,11 +1436,24 @@ __device__ __forceinline__ void combine_block(const SweepCommon& c, const SweepB
   for (int e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
     const int i = e % g.ni, jk = e / g.ni;
     const uint32_t p = (uint32_t)at(g, i, jk % g.nj, jk / g.nj);
-    R r[5];
+    R part[3][5], r[5];  // zeta, eta, xi
 #pragma unroll
-    for (int v = 0; v < 5; ++v)
-      r[v] = ldg(plane_ptr(rt, (10 + v) * g.plane), p) +
-             (ldg(plane_ptr(rt, (5 + v) * g.plane), p) + ldg(plane_ptr(rt, v * g.plane), p));
+    for (int d = 0; d < 3; ++d)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) part[d][v] = ldg(plane_ptr(rt, (5 * d + v) * g.plane), p);
+    if constexpr (WITH_VISC) {
+      const GP<const R> vis = to_global(static_cast<const R*>(b.vis));
+      const uint32_t st[3] = {(uint32_t)(g.ld_i * g.ld_j), (uint32_t)g.ld_i, 1u};
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int v = 1; v < 5; ++v) {
+          const GP<const R> vp = plane_ptr(vis, (4 * (2 - d) + v - 1) * g.plane);
+          part[d][v] += d6<R>([&](int m) { return ldg(vp, p + (uint32_t)m * st[d]); });
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) r[v] = part[2][v] + (part[1][v] + part[0][v]);
     const double Jo = ldg(plane_ptr(to_global(b.met), 9 * g.plane), p);
     const GP<double> out = to_global(b.out);
     if (c.out_kind == kOutRhs) {
@@ -1432,21 +1473,30 @@ __device__ __forceinline__ void combine_block(const SweepCommon& c, const SweepB
     }
   }
 }
-template <typename R>
+template <typename R, bool WITH_VISC>
 __global__ __launch_bounds__(256) void k_combine(SweepCommon c, SweepBlock b) {
-  combine_block<R>(c, b);
+  combine_block<R, WITH_VISC>(c, b);
 }
-template <typename R>
+template <typename R, bool WITH_VISC>
 __global__ __launch_bounds__(256) void k_combine_batch(const SweepBlock* __restrict__ blocks, SweepCommon c) {
-  combine_block<R>(c, blocks[blockIdx.y]);
+  combine_block<R, WITH_VISC>(c, blocks[blockIdx.y]);
 }
 
 template <typename R>
-hipError_t launch_sweep_all(const SweepArgs& a, hipStream_t s) {
+hipError_t launch_sweep_all(const ViscArgs* visc, const SweepArgs& a, hipStream_t s) {
   const Geom& g = a.b.g;
+  ViscArgs va;
+  int nv = 0;
+  if (visc) {
+    va = *visc;
+    bool small;
+    visc_plan(&va.g, 1, false, sizeof(R) == 8, &small, &va.kc, &nv);
+    if (!small) return hipErrorInvalidValue;  // the blocks of this form are far below the line
+  }
   SweepCommon part = a.c;
   part.has_prev = 0;
   part.out_kind = kOutPartial;
+  if (visc) part.do_vis = 0;
   AllBlocks all;
   int n[3];
   for (int d = 0; d < 3; ++d) {
@@ -1455,32 +1505,66 @@ hipError_t launch_sweep_all(const SweepArgs& a, hipStream_t s) {
     n[d] = b.tiles_c1 * b.tiles_d * (d == 2 ? g.nj : g.nk);
     b.rt_out = static_cast<R*>(a.b.rt_out) + (2 - d) * 5 * g.plane;
   }
-  hipLaunchKernelGGL((k_sweep_all<R>), dim3(n[0] + n[1] + n[2]), dim3(kAllNT), 0, s, part, all, n[2], n[1]);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int total = g.ni * g.nj * g.nk;
-  hipLaunchKernelGGL((k_combine<R>), dim3((total + 255) / 256), dim3(256), 0, s, a.c, a.b);
+  const dim3 grid(nv + n[0] + n[1] + n[2]), wg(kAllNT);
+  if (visc)
+    hipLaunchKernelGGL((k_sweep_all<R, true>), grid, wg, 0, s, va, part, all, nv, n[2], n[1]);
+  else
+    hipLaunchKernelGGL((k_sweep_all<R, false>), grid, wg, 0, s, va, part, all, nv, n[2], n[1]);
   return hipGetLastError();
 }
-template hipError_t launch_sweep_all<double>(const SweepArgs&, hipStream_t);
-template hipError_t launch_sweep_all<float>(const SweepArgs&, hipStream_t);
+template hipError_t launch_sweep_all<double>(const ViscArgs*, const SweepArgs&, hipStream_t);
+template hipError_t launch_sweep_all<float>(const ViscArgs*, const SweepArgs&, hipStream_t);
 
 template <typename R>
-hipError_t launch_sweep_all_batch(const SweepBlock* blocks, const SweepCommon& c, const TileList tl[3], int max_points,
-                                  hipStream_t s) {
+hipError_t launch_combine(bool with_visc, const SweepArgs& a, hipStream_t s) {
+  const dim3 grid((a.b.g.ni * a.b.g.nj * a.b.g.nk + 255) / 256), wg(256);
+  if (with_visc)
+    hipLaunchKernelGGL((k_combine<R, true>), grid, wg, 0, s, a.c, a.b);
+  else
+    hipLaunchKernelGGL((k_combine<R, false>), grid, wg, 0, s, a.c, a.b);
+  return hipGetLastError();
+}
+template hipError_t launch_combine<double>(bool, const SweepArgs&, hipStream_t);
+template hipError_t launch_combine<float>(bool, const SweepArgs&, hipStream_t);
+
+template <typename R>
+hipError_t launch_sweep_all_batch(const ViscArgs* visc, const TileList* visc_tl, const SweepBlock* blocks,
+                                  const SweepCommon& c, const TileList tl[3], hipStream_t s) {
   const int nb = tl[0].nblk;
   SweepCommon part = c;
   part.has_prev = 0;
   part.out_kind = kOutPartial;
+  AllLists l{};
+  l.x = tl[0];
+  l.e = tl[1];
+  l.z = tl[2];
   const int n = tl[0].prefix[nb] + tl[1].prefix[nb] + tl[2].prefix[nb];
-  hipLaunchKernelGGL((k_sweep_all_batch<R>), dim3(n), dim3(kAllNT), 0, s, blocks, part, tl[0], tl[1], tl[2]);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_combine_batch<R>), dim3((max_points + 255) / 256, nb), dim3(256), 0, s, blocks, c);
+  if (visc) {
+    part.do_vis = 0;
+    l.v = *visc_tl;
+    hipLaunchKernelGGL((k_sweep_all_batch<R, true>), dim3(l.v.prefix[nb] + n), dim3(kAllNT), 0, s, visc, blocks, part, l);
+  } else {
+    hipLaunchKernelGGL((k_sweep_all_batch<R, false>), dim3(n), dim3(kAllNT), 0, s, visc, blocks, part, l);
+  }
   return hipGetLastError();
 }
-template hipError_t launch_sweep_all_batch<double>(const SweepBlock*, const SweepCommon&, const TileList[3], int, hipStream_t);
-template hipError_t launch_sweep_all_batch<float>(const SweepBlock*, const SweepCommon&, const TileList[3], int, hipStream_t);
+template hipError_t launch_sweep_all_batch<double>(const ViscArgs*, const TileList*, const SweepBlock*, const SweepCommon&,
+                                                   const TileList[3], hipStream_t);
+template hipError_t launch_sweep_all_batch<float>(const ViscArgs*, const TileList*, const SweepBlock*, const SweepCommon&,
+                                                  const TileList[3], hipStream_t);
+
+template <typename R>
+hipError_t launch_combine_batch(bool with_visc, const SweepBlock* blocks, const SweepCommon& c, int nb, int max_points,
+                                hipStream_t s) {
+  const dim3 grid((max_points + 255) / 256, nb), wg(256);
+  if (with_visc)
+    hipLaunchKernelGGL((k_combine_batch<R, true>), grid, wg, 0, s, blocks, c);
+  else
+    hipLaunchKernelGGL((k_combine_batch<R, false>), grid, wg, 0, s, blocks, c);
+  return hipGetLastError();
+}
+template hipError_t launch_combine_batch<double>(bool, const SweepBlock*, const SweepCommon&, int, int, hipStream_t);
+template hipError_t launch_combine_batch<float>(bool, const SweepBlock*, const SweepCommon&, int, int, hipStream_t);
 
 // =====================================================================================
 // Marching sweep (FP64, eta and zeta, partial sums): one thread per grid line, lanes along i.

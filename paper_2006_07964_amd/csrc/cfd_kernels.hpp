@@ -111,18 +111,26 @@ template <typename R>
 hipError_t launch_sweep(int dir, SweepArgs a, hipStream_t s, int cfg = 0);
 
 // All three sweeps of a small block (modified scheme, no one-sided closure) in one launch into
-// three sets of partial sums (rt_in = rt_out: 15 planes), and a launch that adds them and
-// writes R or the RK stage
+// three sets of partial sums (rt_in = rt_out: 15 planes); visc: the viscous prepass in the same
+// launch, the sums inviscid (else visc null and the sums complete)
 struct AllBlocks {
   SweepBlock b[3];
 };
 constexpr int kAllCfg[2][3] = {{5, 6, 6}, {5, 2, 2}};  // tile configurations [FP64 / mixed][direction]
 template <typename R>
-hipError_t launch_sweep_all(const SweepArgs& a, hipStream_t s);
-// blocks: nb xi blocks, nb eta, nb zeta, tiled by kAllCfg (tl likewise); c of the xi sweep
+hipError_t launch_sweep_all(const ViscArgs* visc, const SweepArgs& a, hipStream_t s);
+// the launch that adds them (with_visc: after the derivatives of the viscous fluxes) and writes
+// R or the RK stage
 template <typename R>
-hipError_t launch_sweep_all_batch(const SweepBlock* blocks, const SweepCommon& c, const TileList tl[3], int max_points,
-                                  hipStream_t s);
+hipError_t launch_combine(bool with_visc, const SweepArgs& a, hipStream_t s);
+// blocks: nb xi blocks, nb eta, nb zeta, tiled by kAllCfg (tl likewise); c of the xi sweep; visc
+// (small tiles, visc_tl) may be null
+template <typename R>
+hipError_t launch_sweep_all_batch(const ViscArgs* visc, const TileList* visc_tl, const SweepBlock* blocks,
+                                  const SweepCommon& c, const TileList tl[3], hipStream_t s);
+template <typename R>
+hipError_t launch_combine_batch(bool with_visc, const SweepBlock* blocks, const SweepCommon& c, int nb, int max_points,
+                                hipStream_t s);
 
 // FP64 xi sweep, one wave per line
 hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s);

@@ -1,5 +1,5 @@
-"""The three sweeps of a small block in one launch, and the sum that follows, against the
-sequential sweeps that a block runs once the caller has set its tiles.  The shapes are the
+"""The prepass and the three sweeps of a small block in one launch, and the sum that follows,
+against the sequential launches that a block runs once the caller has set its tiles.  The shapes are the
 same, so every partial sum is, and they are added in the same order: the right-hand side and
 the RK stages (host, device and per-point time steps) agree bit for bit, up to the sizes where
 the form ends (300k points in FP64, 600k in mixed precision)."""
@@ -43,6 +43,33 @@ def test_one_launch_matches_sequential_sweeps(size, viscous, precision):
             B.cfd_block_set_local_dt(d.h, None)
         np.testing.assert_array_equal(a.host(a.qa), b.host(b.qa))
         np.testing.assert_array_equal(a.host(a.qb), b.host(b.qb))
+    finally:
+        a.close()
+        b.close()
+
+
+@pytest.mark.parametrize("precision", [B.CFD_FP64, B.CFD_MIXED])
+def test_one_launch_between_walls(precision):
+    # the viscous ghosts of the walls are filled between the launch and the sum, and the split
+    # form takes them from the fluxes that it is given
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = W.channel(37, 30, 19)
+    a, b = DevBlock(wl, precision=precision), DevBlock(wl, precision=precision)
+    try:
+        B.cfd_block_set_tiles(b.h, [5, 6, 6] if precision == B.CFD_FP64 else [5, 2, 2])
+        want = b.rhs()
+        np.testing.assert_array_equal(a.rhs(), want)
+        inviscid = B.CFD_ALL & ~B.CFD_TERM_VIS
+        np.testing.assert_array_equal(a.rhs(inviscid), b.rhs(inviscid))
+        B.cfd_viscous_fluxes(a.h, a.q)
+        a.r.zero_()
+        B.cfd_rhs_sweeps(a.h, a.q, a.r)
+        np.testing.assert_array_equal(a.host(a.r), want)
+        for d in (a, b):
+            d.step(1e-3)
+        np.testing.assert_array_equal(a.host(a.q), b.host(b.q))
     finally:
         a.close()
         b.close()
