@@ -147,8 +147,8 @@ const char* cfd_last_error(void);
 
 /* ---- blocks ------------------------------------------------------------------------ */
 /* Create a block: validates d, allocates the 10 metric planes (Sec. 2, Eqs 7-8) and the
- * scratch of the RHS (12 viscous-flux planes, Eqs 5-6, and 5 partial-sum planes, in the
- * compute type; a CFD_MIXED block also keeps the metric planes rounded to FP32 for its
+ * scratch of the RHS (12 viscous-flux planes, Eqs 5-6, and 5 partial-sum planes, 15 for a
+ * small block whose three sweeps run in one launch, in the compute type; a CFD_MIXED block also keeps the metric planes rounded to FP32 for its
  * FP32 arithmetic, and the metrics of the half points between nodes, which Sec. 4.5
  * interpolates from the node values where they are used, interpolated once in FP64 and
  * rounded) on the current device.  hip_stream (hipStream_t, may be NULL =
@@ -314,7 +314,8 @@ int cfd_batch_step(cfd_batch* bt, const double* dt_dev, double* const* Qn, doubl
 
 /* Tile configuration chosen per sweep direction (cfg[d] indexes the library's tile
  * shapes, persist[d] = 1 for the persistent schedule).  Before the first step these are
- * the defaults; the first cfd_batch_step times every candidate and keeps the fastest.   */
+ * the defaults; the first cfd_batch_step times every candidate, and for small blocks the
+ * three sweeps in one launch, and keeps the fastest.                                     */
 int cfd_batch_tuning(const cfd_batch* bt, int* cfg, int* persist);
 /* Override the tiling (skips the autotuner; the next step re-captures its graph).
  * CFD_ERR_UNSUPPORTED for a persistent schedule with the original scheme or with blocks
@@ -339,8 +340,10 @@ int cfd_tile_config(int cfg, int* lines, int* nodes, int* threads);
 /* Tile shape per direction (cfg[0..2] for xi, eta, zeta) of a block's own launches
  * (cfd_rhs, cfd_rk_stage, cfd_rhs_sweeps, cfd_rk_sweeps).  Every shape does the same
  * arithmetic per node; each is a separately compiled kernel whose multiply-add
- * contraction may differ, so shapes agree to round-off.  The default is the library's
- * choice for large blocks.                                                               */
+ * contraction may differ, so shapes agree to round-off.  Until it is called, a block runs
+ * the library's own choice by its size and precision: these shapes, marching sweeps that
+ * give each thread a grid line, or all three sweeps in one launch (cfd_block_tiles gives
+ * the shapes of the first).                                                              */
 int cfd_block_set_tiles(cfd_block* b, const int* cfg);
 int cfd_block_tiles(const cfd_block* b, int* cfg);
 

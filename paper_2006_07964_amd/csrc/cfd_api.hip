@@ -133,6 +133,7 @@ constexpr int64_t kAllPoints[2] = {300000, 600000};
 // 80^3 272 / 273.  Batches: FP64 8 blocks of 10k points in all 125 / 114, 6 of 97k 208 / 200,
 // 24 of 118k 241 / 248; mixed 8 of 10k 117 / 108, 12 of 184k 238 / 225
 constexpr int64_t kFusedPoints[2] = {110000, 600000};
+constexpr int kPinDt = 10, kPinFlag = 11, kPinCount = 12;  // after the residual's ten
 
 struct cfd_block {
   cfd_block_desc d;
@@ -166,7 +167,10 @@ struct cfd_block {
   int* flag_dev = nullptr;
   double* res_dev = nullptr;  // residual partial rows of up to kMaxBlocks blocks (allocated on first use)
   const double* dt_field = nullptr;  // caller's per-point time steps (local time stepping) or null
-  double* pin = nullptr;  // pinned host memory the reductions write their results to (allocated on first use)
+  // pinned host memory that the synchronising reductions write their few numbers to, which the
+  // wait that follows makes visible (a copy from device memory costs another 8 us): ten of the
+  // residual, the time step, the finiteness flag
+  double* pin = nullptr;
   hipEvent_t ev = nullptr;    // orders this block's stream before another block's
   Profiler prof;
 };
@@ -572,18 +576,6 @@ int check_rk_args(cfd_block* b, int stage, const double* Qn, const double* Qcur,
   return CFD_OK;
 }
 
-// Pinned host memory of a block's synchronising reductions: the last kernel writes its few
-// numbers there, which the wait that follows makes visible (a copy from device memory costs
-// another 8 us).
-int pinned_results(cfd_block* b) {
-  if (b->pin) return CFD_OK;
-  if (hipHostMalloc((void**)&b->pin, 16 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-    b->pin = nullptr;
-    return fail(CFD_ERR_ALLOC, "pinned result memory");
-  }
-  return CFD_OK;
-}
-
 // Residual scratch of cfd_residual_noalloc: kResGroups partial rows of up to kMaxBlocks
 // blocks and the 10 results, in a file-scope device array (1.31 MB per device, held until
 // the process ends).  Host code never uses the array's name as an address: the device
@@ -652,7 +644,8 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
                   (int64_t)d->ni * d->nj * d->nk <= kAllPoints[b->esize == sizeof(double) ? 0 : 1];
   if (aligned_planes(plane, b->all_sweeps ? 15 : 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
   if (hipMalloc((void**)&b->red_dev, sizeof(unsigned long long)) != hipSuccess ||
-      hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess)
+      hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess ||
+      hipHostMalloc((void**)&b->pin, kPinCount * sizeof(double), hipHostMallocDefault) != hipSuccess)
     return cleanup(CFD_ERR_ALLOC, "reduction scratch");
   if (hipEventCreateWithFlags(&b->ev, hipEventDisableTiming) != hipSuccess) return cleanup(CFD_ERR_HIP, "block event");
   const int planes = (b->esize == sizeof(double) ? 17 : 36) + (b->all_sweeps ? 10 : 0);
@@ -803,11 +796,10 @@ int cfd_sync(cfd_block* b) {
 
 int cfd_check_finite(cfd_block* b, const double* Q, int* ok) {
   if (!b || !Q || !ok) return fail(CFD_ERR_ARG, "null argument");
-  int rc = pinned_results(b);
-  if (rc != CFD_OK) return rc;
-  volatile int* flag = reinterpret_cast<volatile int*>(b->pin);
+  int* pin = reinterpret_cast<int*>(b->pin + kPinFlag);
+  volatile int* flag = pin;
   *flag = 0;
-  HIP_TRY(launch_finite(b->g, Q, reinterpret_cast<int*>(b->pin), b->stream), "finite check launch");
+  HIP_TRY(launch_finite(b->g, Q, pin, b->stream), "finite check launch");
   HIP_TRY(hipStreamSynchronize(b->stream), "stream synchronize");
   *ok = *flag ? 0 : 1;
   return *ok ? CFD_OK : fail(CFD_ERR_NONFINITE, "non-finite value in state");
@@ -841,11 +833,10 @@ int cfd_dt_cfl(cfd_block* const* blocks, int nb, const double* const* Q, double 
   // the reduction runs on the first block's stream: finish earlier work of the others
   for (int n = 1; n < nb; ++n)
     if (blocks[n]->stream != b0->stream) HIP_TRY(hipStreamSynchronize(blocks[n]->stream), "stream synchronize");
-  int rc = pinned_results(b0);
-  if (rc == CFD_OK) rc = dt_launches(blocks, nb, Q, cfl, b0->pin);
+  const int rc = dt_launches(blocks, nb, Q, cfl, b0->pin + kPinDt);
   if (rc != CFD_OK) return rc;
   HIP_TRY(hipStreamSynchronize(b0->stream), "stream synchronize");
-  const double dt = *static_cast<volatile double*>(b0->pin);
+  const double dt = *static_cast<volatile double*>(b0->pin + kPinDt);
   if (std::isnan(dt)) return fail(CFD_ERR_NONFINITE, "spectral radius is not positive and finite");
   *dt_out = dt;
   return CFD_OK;
@@ -911,8 +902,7 @@ int cfd_residual(cfd_block* const* blocks, int nb, const double* const* A, const
       return fail(CFD_ERR_ALLOC, "residual scratch");
     }
   }
-  int rc = pinned_results(b0);
-  if (rc == CFD_OK) rc = order_on_first(blocks, nb);
+  const int rc = order_on_first(blocks, nb);
   if (rc != CFD_OK) return rc;
   for (int n = 0; n < nb; ++n)
     HIP_TRY(launch_res_partial(blocks[n]->g, A[n], Bm ? Bm[n] : nullptr, scale, b0->res_dev + (int64_t)n * kResGroups * 10,

@@ -1076,8 +1076,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
   __shared__ SweepShared<R, TW, TS> sh;
   sweep_tile<DIR, R, TW, TS, NT, SCHEME, OS>(a.c, a.b, xcd_remap(blockIdx.x, gridDim.x), sh);
 }
-// the original scheme in FP64 holds six stencil points and the half-point basis at once:
-// three waves per SIMD give it the registers that four would make it spill
+// the original scheme in FP64 holds five projected differences and the half-point basis at
+// once (141-160 VGPRs): three waves per SIMD give it what four would make it spill
 template <int DIR, typename R, int TW, int TS, int NT, bool OS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_sweep_w3(SweepArgs a) {
   __shared__ SweepShared<R, TW, TS> sh;
