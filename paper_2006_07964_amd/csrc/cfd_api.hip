@@ -162,8 +162,7 @@ struct cfd_block {
   int cfg[3] = {0, 0, 0};  // sweep tile shape per direction (set at creation)
   bool own_tiles = false;  // the caller chose the shapes: every sweep runs them
   // small device scratch for reductions
-  unsigned long long* red_dev = nullptr;
-  bool red_dirty = true;  // red_dev is not known to be cleared
+  unsigned long long* red_dev = nullptr;  // kDtSlots
   int* flag_dev = nullptr;
   double* res_dev = nullptr;  // residual partial rows of up to kMaxBlocks blocks (allocated on first use)
   const double* dt_field = nullptr;  // caller's per-point time steps (local time stepping) or null
@@ -643,7 +642,7 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
   b->all_sweeps = d->params.scheme == CFD_AFWENO_MODIFIED && !one_sided_mask(*d) &&
                   (int64_t)d->ni * d->nj * d->nk <= kAllPoints[b->esize == sizeof(double) ? 0 : 1];
   if (aligned_planes(plane, b->all_sweeps ? 15 : 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
-  if (hipMalloc((void**)&b->red_dev, sizeof(unsigned long long)) != hipSuccess ||
+  if (hipMalloc((void**)&b->red_dev, kDtSlots * sizeof(unsigned long long)) != hipSuccess ||
       hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess ||
       hipHostMalloc((void**)&b->pin, kPinCount * sizeof(double), hipHostMallocDefault) != hipSuccess)
     return cleanup(CFD_ERR_ALLOC, "reduction scratch");
@@ -805,19 +804,16 @@ int cfd_check_finite(cfd_block* b, const double* Q, int* ok) {
   return *ok ? CFD_OK : fail(CFD_ERR_NONFINITE, "non-finite value in state");
 }
 
-// The step of all blocks on the first block's stream, written to *dt (device or pinned
-// memory).  The accumulator is cleared by the launch that reads it, so it needs clearing only
-// before its first use and after a call that failed between launches.
+// The step of all blocks on the first block's stream, written to *dt (device or pinned memory).
 static int dt_launches(cfd_block* const* blocks, int nb, const double* const* Q, double cfl, double* dt) {
   cfd_block* b0 = blocks[0];
-  if (b0->red_dirty) HIP_TRY(launch_dt_reset(b0->red_dev, b0->stream), "dt reset launch");
-  b0->red_dirty = true;
+  int nslots = 0;
+  for (int n = 0; n < nb; ++n) nslots = std::max(nslots, dt_slots(blocks[n]->g));
   for (int n = 0; n < nb; ++n) {
     cfd_block* b = blocks[n];
-    HIP_TRY(launch_dt_max(b->g, Q[n], b->met, b->d.params.gamma, b0->red_dev, b0->stream), "dt launch");
+    HIP_TRY(launch_dt_max(b->g, Q[n], b->met, b->d.params.gamma, n == 0, nslots, b0->red_dev, b0->stream), "dt launch");
   }
-  HIP_TRY(launch_dt_finish(b0->red_dev, cfl, dt, b0->stream), "dt finish launch");
-  b0->red_dirty = false;
+  HIP_TRY(launch_dt_finish(b0->red_dev, nslots, cfl, dt, b0->stream), "dt finish launch");
   return CFD_OK;
 }
 

@@ -187,15 +187,18 @@ template <typename T>
 hipError_t launch_visc_ghost(const BcSeg* segs_dev, int nseg, int max_elems, const PtrTable& t, hipStream_t s);
 
 // ---- reductions ---------------------------------------------------------------------
-// maximum of the spectral radius over one block, as a bit pattern, into acc (zero before)
-hipError_t launch_dt_max(const Geom& g, const double* q, const double* met, double gamma,
-                         unsigned long long* acc, hipStream_t s);
-// *dt (device or pinned memory) receives cfl / maximum, NaN when that is not positive and
-// finite; acc is cleared
-hipError_t launch_dt_finish(unsigned long long* acc, double cfl, double* dt, hipStream_t s);
+// A CFL step: one launch_dt_max per block, first set for the first of them, then
+// launch_dt_finish, all with the same nslots, at least the dt_slots of every block.  The slots
+// hold the workgroups' maxima of the spectral radius as bit patterns; what they held before
+// does not matter.  *dt (device or pinned memory) receives cfl / maximum, NaN when that is not
+// positive and finite.
+constexpr int kDtSlots = 2048;
+int dt_slots(const Geom& g);
+hipError_t launch_dt_max(const Geom& g, const double* q, const double* met, double gamma, bool first, int nslots,
+                         unsigned long long* slots, hipStream_t s);
+hipError_t launch_dt_finish(const unsigned long long* slots, int nslots, double cfl, double* dt, hipStream_t s);
 // *flag (device or pinned memory) is set to 1 if an interior value is not finite
 hipError_t launch_finite(const Geom& g, const double* q, int* flag, hipStream_t s);
-hipError_t launch_dt_reset(unsigned long long* acc, hipStream_t s);
 hipError_t launch_dt_local(const Geom& g, const double* q, const double* met, double gamma, double cfl,
                            double* dt_field, hipStream_t s);
 // residual norms: kResGroups partial rows (10 doubles: 5 sums of squares, 5 maxima) per
