@@ -2310,16 +2310,17 @@ hipError_t launch_dt_finish(const unsigned long long* slots, int nslots, double 
 // scale * (a - b) (b may be null); lanes -> wave: a fixed-order shuffle tree; waves ->
 // workgroup: their rows in LDS in order; the kResGroups partial rows of every block are then
 // reduced by one workgroup, again in a fixed order, so the result does not depend on timing.
-// Bound by HBM reads: sixteen waves per workgroup, one workgroup per CU, keep ten loads per
-// lane in flight (four waves did not: 224 x 200 x 176 with b, 348 us at 1.8 TB/s).
-constexpr int kResNT = 1024;
-__global__ __launch_bounds__(kResNT) void k_res_partial(Geom g, const double* __restrict__ a, const double* __restrict__ b,
-                                                        double scale, double* __restrict__ part) {
-  __shared__ double red[kResNT / 64][10];
+// Bound by HBM reads where there are enough: sixteen waves per workgroup, one workgroup per CU,
+// keep ten loads per lane in flight (with four, the call on 256^3 with b took 668 us, now 268).
+// Small blocks take four waves (residual_waves).
+template <int NT>
+__global__ __launch_bounds__(NT) void k_res_partial(Geom g, const double* __restrict__ a, const double* __restrict__ b,
+                                                    double scale, double* __restrict__ part) {
+  __shared__ double red[NT / 64][10];
   double sq[5] = {0, 0, 0, 0, 0}, mx[5] = {0, 0, 0, 0, 0};
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lines = g.nj * g.nk;
-  for (int l = blockIdx.x * (kResNT / 64) + wave; l < lines; l += gridDim.x * (kResNT / 64)) {
+  for (int l = blockIdx.x * (NT / 64) + wave; l < lines; l += gridDim.x * (NT / 64)) {
     const int64_t line = at(g, 0, l % g.nj, l / g.nj);
     for (int i = lane; i < g.ni; i += 64) {
       const int64_t p = line + i;
@@ -2350,7 +2351,7 @@ __global__ __launch_bounds__(kResNT) void k_res_partial(Geom g, const double* __
   __syncthreads();
   if (threadIdx.x < 10) {
     double r = red[0][threadIdx.x];
-    for (int w = 1; w < kResNT / 64; ++w) r = threadIdx.x < 5 ? r + red[w][threadIdx.x] : fmax(r, red[w][threadIdx.x]);
+    for (int w = 1; w < NT / 64; ++w) r = threadIdx.x < 5 ? r + red[w][threadIdx.x] : fmax(r, red[w][threadIdx.x]);
     part[(int64_t)blockIdx.x * 10 + threadIdx.x] = r;
   }
 }
@@ -2386,9 +2387,22 @@ __global__ __launch_bounds__(256) void k_res_final(const double* __restrict__ pa
   else if (threadIdx.x < 10) out[threadIdx.x] = red[threadIdx.x][0];
 }
 
+// Waves of a workgroup: four times as many cost 3.5 us more to start and finish, and save that
+// once a wave of the smaller launch makes four more passes over 64 nodes than one of the larger.
+// Call with 4 / 16 waves and b: 32^3 30.4 / 34.4 us, 64^3 33.7 / 34.6, 128 x 64 x 48 39.2 / 36.9,
+// 80^3 52.5 / 41.5, 512 x 32 x 32 43.3 / 47.6, 512 x 64 x 64 84 / 57; 64 blocks of 10^3 402 / 639.
+static int residual_waves(const Geom& g) {
+  const int64_t lines = (int64_t)g.nj * g.nk, row = (g.ni + 63) / 64;
+  auto passes = [&](int waves) { return (lines + kResGroups * waves - 1) / (kResGroups * waves) * row; };
+  return passes(4) - passes(16) < 4 ? 4 : 16;
+}
+
 hipError_t launch_res_partial(const Geom& g, const double* a, const double* b, double scale, double* part,
                               hipStream_t s) {
-  hipLaunchKernelGGL(k_res_partial, dim3(kResGroups), dim3(kResNT), 0, s, g, a, b, scale, part);
+  if (residual_waves(g) == 4)
+    hipLaunchKernelGGL(k_res_partial<256>, dim3(kResGroups), dim3(256), 0, s, g, a, b, scale, part);
+  else
+    hipLaunchKernelGGL(k_res_partial<1024>, dim3(kResGroups), dim3(1024), 0, s, g, a, b, scale, part);
   return hipGetLastError();
 }
 hipError_t launch_res_final(const double* part, int nparts, double inv_n, double* out, hipStream_t s) {
