@@ -10,6 +10,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -133,7 +134,8 @@ constexpr int64_t kAllPoints[2] = {300000, 600000};
 // 80^3 272 / 273.  Batches: FP64 8 blocks of 10k points in all 125 / 114, 6 of 97k 208 / 200,
 // 24 of 118k 241 / 248; mixed 8 of 10k 117 / 108, 12 of 184k 238 / 225
 constexpr int64_t kFusedPoints[2] = {110000, 600000};
-constexpr int kPinDt = 10, kPinFlag = 11, kPinCount = 12;  // after the residual's ten
+constexpr int kPinDt = 10, kPinFlag = 11;  // after the residual's ten
+constexpr int kPinSlot = 16, kPinSlots = 32;  // doubles of a block's slot, slots of a page
 
 struct cfd_block {
   cfd_block_desc d;
@@ -168,7 +170,7 @@ struct cfd_block {
   const double* dt_field = nullptr;  // caller's per-point time steps (local time stepping) or null
   // pinned host memory that the synchronising reductions write their few numbers to, which the
   // wait that follows makes visible (a copy from device memory costs another 8 us): ten of the
-  // residual, the time step, the finiteness flag
+  // residual, the time step, the finiteness flag (a slot of pin_acquire)
   double* pin = nullptr;
   hipEvent_t ev = nullptr;    // orders this block's stream before another block's
   Profiler prof;
@@ -575,6 +577,56 @@ int check_rk_args(cfd_block* b, int stage, const double* Qn, const double* Qcur,
   return CFD_OK;
 }
 
+// Pinned result slots, in pages that the blocks of a device share, because page-locked memory is
+// slow to allocate (29 us) and slower to release: with an allocation per block, creating 24
+// blocks of 5000 points took 2.4 ms and destroying them 7.0 (now 1.5 and 0.7).  A page is
+// allocated when no slot of its device is free and released with its last slot.
+struct PinPage {
+  PinPage* next;
+  double* slots;
+  uint32_t used;  // bit n: slot n has an owner
+  int device;
+};
+static_assert(kPinSlots == 32 && kPinSlot > kPinFlag, "one bit per slot, room for every result");
+std::mutex g_pin_mu;
+PinPage* g_pin_pages = nullptr;
+
+// a slot for a block on the current device, null when pinned memory cannot be had
+double* pin_acquire(int device) {
+  std::lock_guard<std::mutex> lock(g_pin_mu);
+  PinPage* p = g_pin_pages;
+  while (p && (p->device != device || p->used == ~0u)) p = p->next;
+  if (!p) {
+    p = new (std::nothrow) PinPage{g_pin_pages, nullptr, 0, device};
+    if (!p) return nullptr;
+    if (hipHostMalloc((void**)&p->slots, kPinSlots * kPinSlot * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+      delete p;
+      return nullptr;
+    }
+    g_pin_pages = p;
+  }
+  int n = 0;
+  while (p->used >> n & 1) ++n;
+  p->used |= 1u << n;
+  return p->slots + n * kPinSlot;
+}
+
+void pin_release(const double* slot) {
+  if (!slot) return;
+  std::lock_guard<std::mutex> lock(g_pin_mu);
+  for (PinPage** at = &g_pin_pages; *at; at = &(*at)->next) {
+    PinPage* p = *at;
+    if (slot < p->slots || slot >= p->slots + kPinSlots * kPinSlot) continue;
+    p->used &= ~(1u << ((slot - p->slots) / kPinSlot));
+    if (!p->used) {
+      *at = p->next;
+      (void)hipHostFree(p->slots);
+      delete p;
+    }
+    return;
+  }
+}
+
 // Residual scratch of cfd_residual_noalloc: kResGroups partial rows of up to kMaxBlocks
 // blocks and the 10 results, in a file-scope device array (1.31 MB per device, held until
 // the process ends).  Host code never uses the array's name as an address: the device
@@ -643,8 +695,7 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
                   (int64_t)d->ni * d->nj * d->nk <= kAllPoints[b->esize == sizeof(double) ? 0 : 1];
   if (aligned_planes(plane, b->all_sweeps ? 15 : 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
   if (hipMalloc((void**)&b->red_dev, kDtSlots * sizeof(unsigned long long)) != hipSuccess ||
-      hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess ||
-      hipHostMalloc((void**)&b->pin, kPinCount * sizeof(double), hipHostMallocDefault) != hipSuccess)
+      hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess || !(b->pin = pin_acquire(b->device)))
     return cleanup(CFD_ERR_ALLOC, "reduction scratch");
   if (hipEventCreateWithFlags(&b->ev, hipEventDisableTiming) != hipSuccess) return cleanup(CFD_ERR_HIP, "block event");
   const int planes = (b->esize == sizeof(double) ? 17 : 36) + (b->all_sweeps ? 10 : 0);
@@ -674,7 +725,7 @@ int cfd_block_destroy(cfd_block* b) {
   (void)hipFree(b->red_dev);
   (void)hipFree(b->flag_dev);
   (void)hipFree(b->res_dev);
-  if (b->pin) (void)hipHostFree(b->pin);
+  pin_release(b->pin);
   if (b->ev) (void)hipEventDestroy(b->ev);
   (void)hipFree(b->local_bc_dev);
   delete b;
