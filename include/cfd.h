@@ -148,8 +148,8 @@ const char* cfd_last_error(void);
 /* ---- blocks ------------------------------------------------------------------------ */
 /* Create a block: validates d, allocates the 10 metric planes (Sec. 2, Eqs 7-8) and the
  * scratch of the RHS (12 viscous-flux planes, Eqs 5-6, and 5 partial-sum planes, 15 for a
- * small block whose three sweeps run in one launch, in the compute type; a CFD_MIXED block also keeps the metric planes rounded to FP32 for its
- * FP32 arithmetic, and the metrics of the half points between nodes, which Sec. 4.5
+ * small block whose three sweeps run in one launch, in the compute type; a CFD_MIXED block
+ * also keeps the metric planes rounded to FP32 for its FP32 arithmetic, and the metrics of the half points between nodes, which Sec. 4.5
  * interpolates from the node values where they are used, interpolated once in FP64 and
  * rounded) on the current device.  hip_stream (hipStream_t, may be NULL =
  * default stream) is the stream later calls enqueue on.  Errors: CFD_ERR_ARG,
@@ -312,19 +312,25 @@ int cfd_batch_destroy(cfd_batch* bt);
 int cfd_batch_step(cfd_batch* bt, const double* dt_dev, double* const* Qn, double* const* QA,
                    double* const* QB);
 
-/* Tile configuration chosen per sweep direction (cfg[d] indexes the library's tile
- * shapes, persist[d] = 1 for the persistent schedule).  Before the first step these are
- * the defaults; the first cfd_batch_step times every candidate, and for small blocks the
- * three sweeps in one launch, and keeps the fastest.                                     */
+/* Tile configuration chosen per sweep direction: cfg[d] indexes the library's tile shapes;
+ * persist[d] is the schedule, 0 for one workgroup per tile, 1 for the persistent one, and 2
+ * in every direction where the three sweeps of a stage share one launch (small blocks).
+ * Before the first step these are the defaults; the first cfd_batch_step times every
+ * candidate, and for small blocks the one launch, and keeps the fastest.                  */
 int cfd_batch_tuning(const cfd_batch* bt, int* cfg, int* persist);
-/* Override the tiling (skips the autotuner; the next step re-captures its graph).
- * CFD_ERR_UNSUPPORTED for a persistent schedule with the original scheme or with blocks
+/* Override the tiling (skips the autotuner; the next step re-captures its graph).  What
+ * cfd_batch_tuning reported for a batch of the same blocks restores its choice.  The bits
+ * of a step depend on the shapes alone, not on the schedule.  A schedule of 2 in every
+ * direction asks for the one launch where the blocks and the shapes are those it is built
+ * for, and for the persistent schedule elsewhere, like any other value but 0.
+ * CFD_ERR_UNSUPPORTED for a schedule other than 0 with the original scheme or with blocks
  * that use the one-sided viscous closure (those run one workgroup per tile).            */
 int cfd_batch_set_tuning(cfd_batch* bt, const int* cfg, const int* persist);
 /* Milliseconds per launch that the autotuner measured for each candidate, at
  * ms[(d * cfd_tile_config_count() + cfg) * 2 + persist] for sweep direction d; -1 where
  * nothing was measured (the tuner runs on the first step unless cfd_batch_set_tuning
- * came first).  cap is the length of ms, at least 6 * cfd_tile_config_count().          */
+ * came first; the one launch is not among them).  cap is the length of ms, at least
+ * 6 * cfd_tile_config_count().                                                          */
 int cfd_batch_tuning_times(const cfd_batch* bt, float* ms, int cap);
 
 /* Order of the three direction sweeps of an RHS evaluation (dirs[0..2], 0 = xi, 1 = eta,

@@ -134,6 +134,7 @@ constexpr int64_t kAllPoints[2] = {300000, 600000};
 // 80^3 272 / 273.  Batches: FP64 8 blocks of 10k points in all 125 / 114, 6 of 97k 208 / 200,
 // 24 of 118k 241 / 248; mixed 8 of 10k 117 / 108, 12 of 184k 238 / 225
 constexpr int64_t kFusedPoints[2] = {110000, 600000};
+constexpr int kOneLaunch = 2;  // schedule of cfd_batch_tuning: the three sweeps in one launch
 constexpr int kPinDt = 10, kPinFlag = 11;  // after the residual's ten
 constexpr int kPinSlot = 16, kPinSlots = 32;  // doubles of a block's slot, slots of a page
 
@@ -1068,7 +1069,7 @@ struct cfd_batch {
   int cfg[3] = {0, 0, 0};       // tile configuration per direction
   int persist[3] = {0, 0, 0};   // persistent schedule per direction
   bool tuned = false;
-  bool all_sweeps = false;      // the three sweeps of a stage in one launch (the autotuner found it faster)
+  bool all_sweeps = false;      // the three sweeps of a stage in one launch
   float tune_ms[3][kTileCfgs][2];  // autotuner timings (ms per launch, -1: not measured)
   int persist_wgs = 2048;       // workgroups of a persistent launch
   // combined viscous halo work of all blocks: self-periodic + interface copies, ghosts
@@ -1344,6 +1345,13 @@ int upload_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* con
   return CFD_OK;
 }
 
+// every block is small enough for the three sweeps in one launch
+bool can_sweep_all(const cfd_batch* bt) {
+  for (const cfd_block* B : bt->blocks)
+    if (!B->all_sweeps) return false;
+  return true;
+}
+
 // Autotuner: time every (tile configuration, schedule) candidate of each direction's
 // batched sweep on the current state (stage 0 arguments; the RK sweep writes QA, which is
 // scratch at this point) and keep the fastest.
@@ -1400,9 +1408,7 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
     direction_ms[d] = best;
   }
   // the three sweeps of small blocks in one launch, against the fastest three
-  bool all = rc == CFD_OK;
-  for (const cfd_block* B : bt->blocks) all = all && B->all_sweeps;
-  if (all) {
+  if (rc == CFD_OK && can_sweep_all(bt)) {
     int cfg[3], persist[3];
     for (int d = 0; d < 3; ++d) {
       cfg[d] = bt->cfg[d];
@@ -1485,7 +1491,7 @@ int batch_tuning(const cfd_batch* bt, int* cfg, int* persist) {
   if (!bt || !cfg || !persist) return fail(CFD_ERR_ARG, "null argument");
   for (int d = 0; d < 3; ++d) {
     cfg[d] = bt->cfg[d];
-    persist[d] = bt->persist[d];
+    persist[d] = bt->all_sweeps ? kOneLaunch : bt->persist[d];
   }
   return CFD_OK;
 }
@@ -1507,11 +1513,15 @@ int batch_set_tuning(cfd_batch* bt, const int* cfg, const int* persist) {
     for (int d = 0; d < 3; ++d)
       if (persist[d])
         return fail(CFD_ERR_UNSUPPORTED, "the original scheme and one-sided viscous closures have no persistent schedule");
+  // the one launch as cfd_batch_tuning reports it; any other non-zero schedule is the persistent one
+  bool one = can_sweep_all(bt);
+  for (int d = 0; d < 3; ++d)
+    one = one && persist[d] == kOneLaunch && cfg[d] == kAllCfg[bt->precision == CFD_FP64 ? 0 : 1][d];
   for (int d = 0; d < 3; ++d) {
     bt->cfg[d] = cfg[d];
-    bt->persist[d] = persist[d] != 0;
+    bt->persist[d] = !one && persist[d] != 0;
   }
-  bt->all_sweeps = false;
+  bt->all_sweeps = one;
   fill_tiles(bt);
   bt->tuned = true;
   bt->key.clear();  // recapture with the new tiling
