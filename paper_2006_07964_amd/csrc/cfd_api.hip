@@ -1282,8 +1282,8 @@ hipError_t launch_batch_combine(cfd_batch* bt, int st, bool with_visc) {
                                    : launch_combine_batch<float>(with_visc, a, c, nb, most, bt->stream);
 }
 
-// one RK stage of every block (all launches on bt->stream)
-hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
+// the right-hand side of a stage of every block and its update (all launches on bt->stream)
+hipError_t enqueue_rhs(cfd_batch* bt, int st) {
   const int nb = (int)bt->blocks.size();
   hipError_t e = hipSuccess;
   int64_t points = 0;
@@ -1316,6 +1316,13 @@ hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
   } else {
     for (int n = 0; n < 3 && e == hipSuccess; ++n) e = launch_batch_sweep(bt, st, kSweepOrder[n]);
   }
+  return e;
+}
+
+// one RK stage of every block
+hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
+  const int nb = (int)bt->blocks.size();
+  hipError_t e = enqueue_rhs(bt, st);
   if (e != hipSuccess) return e;
   // Q halos of every block: wall reset, interface / periodic copies, ghost fills
   BcArgs ba;
@@ -1336,11 +1343,13 @@ hipError_t enqueue_stage(cfd_batch* bt, int st, double* const* outp) {
   return e;
 }
 
-int upload_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* const* QB, const double* dt_dev) {
+// sweeps_only: the tables of the prepass, which no tile shape changes, are there already
+int upload_args(cfd_batch* bt, double* const* Qn, double* const* QA, double* const* QB, const double* dt_dev,
+                bool sweeps_only = false) {
   std::vector<ViscArgs> va;
   std::vector<SweepBlock> sa;
   build_args(bt, Qn, QA, QB, dt_dev, va, sa);
-  HIP_TRY(hipMemcpy(bt->visc_args_dev, va.data(), va.size() * sizeof(ViscArgs), hipMemcpyHostToDevice), "upload args");
+  if (!sweeps_only) HIP_TRY(hipMemcpy(bt->visc_args_dev, va.data(), va.size() * sizeof(ViscArgs), hipMemcpyHostToDevice), "upload args");
   HIP_TRY(hipMemcpy(bt->sweep_args_dev, sa.data(), sa.size() * sizeof(SweepBlock), hipMemcpyHostToDevice), "upload args");
   return CFD_OK;
 }
@@ -1360,7 +1369,6 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
   HIP_TRY(hipEventCreate(&e0), "event");
   HIP_TRY(hipEventCreate(&e1), "event");
   int rc = CFD_OK;
-  float direction_ms[3] = {0.f, 0.f, 0.f};  // fastest sweep of each direction
   if (bt->viscous) {  // the sweeps read the viscous-flux planes of the state being tuned on
     rc = upload_args(bt, Qn, QA, QB, dt_dev);
     if (rc == CFD_OK) {
@@ -1394,7 +1402,7 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
         bt->cfg[d] = c;
         bt->persist[d] = p;
         fill_tiles(bt);
-        if ((rc = upload_args(bt, Qn, QA, QB, dt_dev)) != CFD_OK) break;
+        if ((rc = upload_args(bt, Qn, QA, QB, dt_dev, true)) != CFD_OK) break;
         const float total = timed([&]() { return launch_batch_sweep(bt, 0, d); });
         if (rc == CFD_OK) bt->tune_ms[d][c][p] = total / 2;
         if (rc == CFD_OK && total < best) {
@@ -1405,10 +1413,16 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
       }
     bt->cfg[d] = best_cfg;
     bt->persist[d] = best_p;
-    direction_ms[d] = best;
   }
-  // the three sweeps of small blocks in one launch, against the fastest three
+  // the three sweeps of small blocks in one launch against the fastest three, each with the
+  // prepass as a step runs it (within the launch, or before it, or before the three)
   if (rc == CFD_OK && can_sweep_all(bt)) {
+    auto stage_ms = [&]() {
+      fill_tiles(bt);
+      if ((rc = upload_args(bt, Qn, QA, QB, dt_dev, true)) != CFD_OK) return 0.f;
+      return timed([&]() { return enqueue_rhs(bt, 0); });
+    };
+    const float three = stage_ms();
     int cfg[3], persist[3];
     for (int d = 0; d < 3; ++d) {
       cfg[d] = bt->cfg[d];
@@ -1417,15 +1431,8 @@ int autotune(cfd_batch* bt, double* const* Qn, double* const* QA, double* const*
       bt->persist[d] = 0;
     }
     bt->all_sweeps = true;
-    fill_tiles(bt);
-    rc = upload_args(bt, Qn, QA, QB, dt_dev);
-    float total = 0.f;
-    if (rc == CFD_OK)
-      total = timed([&]() {
-        const hipError_t e = launch_batch_all(bt, 0, false);
-        return e == hipSuccess ? launch_batch_combine(bt, 0, false) : e;
-      });
-    if (rc != CFD_OK || total >= direction_ms[0] + direction_ms[1] + direction_ms[2]) {
+    const float one = rc == CFD_OK ? stage_ms() : 0.f;
+    if (rc != CFD_OK || one >= three) {
       bt->all_sweeps = false;
       for (int d = 0; d < 3; ++d) bt->cfg[d] = cfg[d], bt->persist[d] = persist[d];
     }
