@@ -164,6 +164,10 @@ struct cfd_block {
   int patched = 0;  // exchanges that connect part of one of its physical faces to a block
   int cfg[3] = {0, 0, 0};  // sweep tile shape per direction (set at creation)
   bool own_tiles = false;  // the caller chose the shapes: every sweep runs them
+  // plans of its own launches, which depend on its sizes alone
+  bool visc_small = false;  // prepass: tile shape, planes per tile, tiles (visc_plan)
+  int visc_kc = 0, visc_tiles = 0;
+  int march[3] = {0, 0, 0};  // chunk length of the marching sweeps, 0: not by lines (march_len)
   // small device scratch for reductions
   unsigned long long* red_dev = nullptr;  // kDtSlots
   int* flag_dev = nullptr;
@@ -441,6 +445,7 @@ ViscArgs visc_args(const cfd_block* b, const double* Q) {
   va.met_r = b->met_r;
   va.vis = b->vis;
   va.ph = make_phys(b->d.params);
+  va.kc = b->visc_kc;
   va.one_sided = one_sided_mask(b->d);
   // the prepass writes the periodic images itself
   for (int ax = 0; ax < 3; ++ax)
@@ -462,7 +467,8 @@ int run_visc_ghosts(cfd_block* b) {
 int run_visc(cfd_block* b, const double* Q) {
   const ViscArgs va = visc_args(b, Q);
   ProfScope ps(&b->prof, "visc_prepass", b->stream);
-  hipError_t e = b->d.precision == CFD_FP64 ? launch_visc<double>(va, b->stream) : launch_visc<float>(va, b->stream);
+  hipError_t e = b->d.precision == CFD_FP64 ? launch_visc<double>(va, b->visc_small, b->visc_tiles, b->stream)
+                                            : launch_visc<float>(va, b->visc_small, b->visc_tiles, b->stream);
   ps.done();
   if (e != hipSuccess) return hip_fail(e, "visc_prepass launch");
   return run_visc_ghosts(b);
@@ -525,15 +531,15 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     a.b.out = out;
     a.c.out_kind = out_kind;
     const bool f64 = b->d.precision == CFD_FP64;
-    const bool fused = with_visc && vis && (int64_t)b->g.ni * b->g.nj * b->g.nk <= kFusedPoints[f64 ? 0 : 1];
+    const bool fused = with_visc && vis && b->visc_small && (int64_t)b->g.ni * b->g.nj * b->g.nk <= kFusedPoints[f64 ? 0 : 1];
     if (with_visc && vis && !fused) {
       const int rc = run_visc(b, Q);
       if (rc) return rc;
     }
     const ViscArgs va = visc_args(b, Q);
     ProfScope ps(&b->prof, out_kind == kOutRK ? "sweeps_rk" : "sweeps", b->stream);
-    hipError_t e = f64 ? launch_sweep_all<double>(fused ? &va : nullptr, a, b->stream)
-                       : launch_sweep_all<float>(fused ? &va : nullptr, a, b->stream);
+    hipError_t e = f64 ? launch_sweep_all<double>(fused ? &va : nullptr, b->visc_tiles, a, b->stream)
+                       : launch_sweep_all<float>(fused ? &va : nullptr, b->visc_tiles, a, b->stream);
     if (e == hipSuccess && fused) {
       const int rc = run_visc_ghosts(b);
       if (rc) return rc;
@@ -552,12 +558,14 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     a.b.out = last ? out : nullptr;
     const char* name = (last && out_kind == kOutRK) ? kSweepRkNames[dirs[n]] : kSweepNames[dirs[n]];
     ProfScope ps(&b->prof, name, b->stream);
-    hipError_t e = hipSuccess;
+    hipError_t e;
     if (b->d.precision != CFD_FP64)
       e = launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
     else if (!b->own_tiles && dirs[n] == 0 && inv)
       e = launch_sweep_rows(a, b->stream);
-    else if (b->own_tiles || !launch_march(dirs[n], a, b->stream, &e))
+    else if (!b->own_tiles && b->march[dirs[n]] && inv && !last)
+      e = launch_march(dirs[n], a, b->march[dirs[n]], b->stream);
+    else
       e = launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
     ps.done();
     if (e != hipSuccess) return hip_fail(e, "sweep launch");
@@ -678,6 +686,9 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
   b->stream = (hipStream_t)hip_stream;
   b->esize = d->precision == CFD_FP64 ? 8 : 4;
   for (int dir = 0; dir < 3; ++dir) b->cfg[dir] = kDefaultTiles[d->precision == CFD_FP64 ? 0 : 1][dir];
+  visc_plan(&b->g, 1, false, d->precision == CFD_FP64, &b->visc_small, &b->visc_kc, &b->visc_tiles);
+  for (int dir = 1; dir < 3; ++dir)
+    if (d->precision == CFD_FP64 && d->params.weights != CFD_WENO_LINEAR) b->march[dir] = march_len(dir, b->g);
   (void)hipGetDevice(&b->device);
   const size_t plane = (size_t)b->g.plane;
   auto cleanup = [&](int code, const std::string& msg) {

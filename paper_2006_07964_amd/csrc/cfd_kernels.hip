@@ -513,18 +513,15 @@ static void launch_visc_shape(const ViscArgs& a, int tiles, hipStream_t s) {
 }
 
 template <typename R>
-hipError_t launch_visc(ViscArgs a, hipStream_t s) {
-  int tiles;
-  bool small;
-  visc_plan(&a.g, 1, false, sizeof(R) == 8, &small, &a.kc, &tiles);
+hipError_t launch_visc(const ViscArgs& a, bool small, int tiles, hipStream_t s) {
   if (small)
     launch_visc_shape<R, true>(a, tiles, s);
   else
     launch_visc_shape<R, false>(a, tiles, s);
   return hipGetLastError();
 }
-template hipError_t launch_visc<double>(ViscArgs, hipStream_t);
-template hipError_t launch_visc<float>(ViscArgs, hipStream_t);
+template hipError_t launch_visc<double>(const ViscArgs&, bool, int, hipStream_t);
+template hipError_t launch_visc<float>(const ViscArgs&, bool, int, hipStream_t);
 
 template <typename R, bool SMALL>
 static void launch_visc_batch_shape(const ViscArgs* args_dev, const TileList& tl, bool one_sided, hipStream_t s) {
@@ -1483,16 +1480,13 @@ __global__ __launch_bounds__(256) void k_combine_batch(const SweepBlock* __restr
 }
 
 template <typename R>
-hipError_t launch_sweep_all(const ViscArgs* visc, const SweepArgs& a, hipStream_t s) {
+hipError_t launch_sweep_all(const ViscArgs* visc, int nv, const SweepArgs& a, hipStream_t s) {
   const Geom& g = a.b.g;
-  ViscArgs va;
-  int nv = 0;
-  if (visc) {
+  ViscArgs va{};
+  if (visc)
     va = *visc;
-    bool small;
-    visc_plan(&va.g, 1, false, sizeof(R) == 8, &small, &va.kc, &nv);
-    if (!small) return hipErrorInvalidValue;  // the blocks of this form are far below the line
-  }
+  else
+    nv = 0;
   SweepCommon part = a.c;
   part.has_prev = 0;
   part.out_kind = kOutPartial;
@@ -1512,8 +1506,8 @@ hipError_t launch_sweep_all(const ViscArgs* visc, const SweepArgs& a, hipStream_
     hipLaunchKernelGGL((k_sweep_all<R, false>), grid, wg, 0, s, va, part, all, nv, n[2], n[1]);
   return hipGetLastError();
 }
-template hipError_t launch_sweep_all<double>(const ViscArgs*, const SweepArgs&, hipStream_t);
-template hipError_t launch_sweep_all<float>(const ViscArgs*, const SweepArgs&, hipStream_t);
+template hipError_t launch_sweep_all<double>(const ViscArgs*, int, const SweepArgs&, hipStream_t);
+template hipError_t launch_sweep_all<float>(const ViscArgs*, int, const SweepArgs&, hipStream_t);
 
 template <typename R>
 hipError_t launch_combine(bool with_visc, const SweepArgs& a, hipStream_t s) {
@@ -1880,7 +1874,8 @@ __global__ __launch_bounds__(kMarchNT) __attribute__((amdgpu_waves_per_eu(2, 2))
   march_lines<DIR, SCHEME, VIS, PREV, OS>(a.c, a.b, t % groups, t / groups, len, sh);
 }
 
-// Chunk length of the marching sweep, or 0 where the tiles are faster.  A workgroup puts one
+// Chunk length of the marching sweep, or 0 where the tiles are faster: a plan of the block,
+// made once (the search takes up to 2 sqrt(nd) lengths).  A workgroup puts one
 // wave on each SIMD of its CU, two keep the SIMDs busy, and a step of a wave takes one unit
 // (2.45 us in eta with a partial sum, 2.2 us in zeta without) of SIMD time; a chunk of len
 // outputs costs len + 2.6 steps (two more WENO nodes, four nodes without), and a launch takes
@@ -1889,20 +1884,22 @@ __global__ __launch_bounds__(kMarchNT) __attribute__((amdgpu_waves_per_eu(2, 2))
 // unit per 47000 points.  Measured eta, tiles / march: 96x80x72 31 / 32 us (tiles kept),
 // 160x88x96 64 / 61, 144x120x100 83 / 79, 192x112x72 74 / 69, 128^3 110 / 89, 190x131x93
 // 125 / 103, 256^3 890 / 641.
-static int march_len(int dir, const Geom& g) {
+int march_len(int dir, const Geom& g) {
   const int nd = dir == 1 ? g.nj : g.nk, n2 = dir == 1 ? g.nk : g.nj;
   const int64_t groups = ((int64_t)g.ni * n2 + kMarchNT - 1) / kMarchNT;
   const double points = (double)g.ni * g.nj * g.nk;
   double best = points / 47000.0;
   int best_len = 0;
-  for (int chunks = 1; chunks <= nd; ++chunks) {
-    int len = (nd + chunks - 1) / chunks;
-    len += len & 1;  // steps come in pairs
+  for (int chunks = 1; chunks <= nd;) {
+    const int part = (nd + chunks - 1) / chunks;
+    const int len = part + (part & 1);  // steps come in pairs
     const int64_t wgs = groups * ((nd + len - 1) / len);
     if (wgs > 16 * 1024 && chunks > 1) break;  // many rounds already
     const int64_t rounds = (wgs + 255) / 256;
     const double cost = (rounds == 1 ? 1.15 : (double)rounds) * (len + 2.6);
     if (cost < best) best = cost, best_len = len;
+    if (part == 1) break;
+    chunks = (nd + part - 2) / (part - 1);  // the first count whose chunks are shorter
   }
   return best_len;
 }
@@ -1930,18 +1927,14 @@ static void launch_march_scheme(const SweepArgs& a, int groups, int chunks, int 
        : launch_march_dir<DIR, kModified, false>(a, groups, chunks, len, s);
 }
 
-bool launch_march(int dir, const SweepArgs& a, hipStream_t s, hipError_t* err) {
-  if (dir == 0 || a.c.out_kind != kOutPartial || !a.c.do_inv || a.c.ph.linear) return false;
-  const int len = march_len(dir, a.b.g);
-  if (!len) return false;
+hipError_t launch_march(int dir, const SweepArgs& a, int len, hipStream_t s) {
   const int nd = dir == 1 ? a.b.g.nj : a.b.g.nk, n2 = dir == 1 ? a.b.g.nk : a.b.g.nj;
   const int groups = (int)(((int64_t)a.b.g.ni * n2 + kMarchNT - 1) / kMarchNT), chunks = (nd + len - 1) / len;
   if (dir == 1)
     launch_march_scheme<1>(a, groups, chunks, len, s);
   else
     launch_march_scheme<2>(a, groups, chunks, len, s);
-  *err = hipGetLastError();
-  return true;
+  return hipGetLastError();
 }
 
 // =====================================================================================

@@ -43,7 +43,7 @@ struct ViscArgs {
                   // nodes next to it)
 };
 template <typename R>
-hipError_t launch_visc(ViscArgs a, hipStream_t s);
+hipError_t launch_visc(const ViscArgs& a, bool small, int tiles, hipStream_t s);
 // dst[e] = float(src[e]) for e < n
 hipError_t launch_round(const double* src, float* dst, int64_t n, hipStream_t s);
 // Half-point metrics of a mixed-precision block: plane 3 d + c of hm holds, at node n along
@@ -111,14 +111,14 @@ template <typename R>
 hipError_t launch_sweep(int dir, SweepArgs a, hipStream_t s, int cfg = 0);
 
 // All three sweeps of a small block (modified scheme, no one-sided closure) in one launch into
-// three sets of partial sums (rt_in = rt_out: 15 planes); visc: the viscous prepass in the same
-// launch, the sums inviscid (else visc null and the sums complete)
+// three sets of partial sums (rt_in = rt_out: 15 planes); visc: the viscous prepass (small tiles)
+// in the same launch, the sums inviscid (else visc null and the sums complete)
 struct AllBlocks {
   SweepBlock b[3];
 };
 constexpr int kAllCfg[2][3] = {{5, 6, 6}, {5, 2, 2}};  // tile configurations [FP64 / mixed][direction]
 template <typename R>
-hipError_t launch_sweep_all(const ViscArgs* visc, const SweepArgs& a, hipStream_t s);
+hipError_t launch_sweep_all(const ViscArgs* visc, int visc_tiles, const SweepArgs& a, hipStream_t s);
 // the launch that adds them (with_visc: after the derivatives of the viscous fluxes) and writes
 // R or the RK stage
 template <typename R>
@@ -135,9 +135,10 @@ hipError_t launch_combine_batch(bool with_visc, const SweepBlock* blocks, const 
 // FP64 xi sweep, one wave per line
 hipError_t launch_sweep_rows(SweepArgs a, hipStream_t s);
 
-// FP64 eta or zeta sweep into partial sums by lines (JS weights, modified scheme, no one-sided
-// closure along dir), where it is faster than the tiles; false: nothing launched
-bool launch_march(int dir, const SweepArgs& a, hipStream_t s, hipError_t* err);
+// FP64 eta or zeta sweep (JS weights, inviscid terms on) into partial sums by lines, in chunks of
+// len outputs; march_len gives the length for a block, 0 where the tiles are faster
+int march_len(int dir, const Geom& g);
+hipError_t launch_march(int dir, const SweepArgs& a, int len, hipStream_t s);
 
 template <typename R>
 hipError_t launch_sweep_batch(int dir, int cfg, bool persist, const SweepBlock* blocks_dev, const SweepCommon& c,
