@@ -291,7 +291,10 @@ def run_leg(torch, B, wl, wname, precision, form, steps, warmup, scheme=0, tiles
         tc, tp = B.cfd_batch_tuning(bt)
         res["tuned_tiles"] = {"cfg": tc, "persistent": tp}
     else:
-        res["tiles"] = B.cfd_block_tiles(hs[0])
+        forms = B.cfd_block_sweep_forms(hs[0])
+        res["sweep_forms"] = [("tiles", "rows", "march", "one launch")[f] for f in forms]
+        if B.CFD_SWEEP_TILES in forms:
+            res["tiles"] = [t if f == B.CFD_SWEEP_TILES else None for t, f in zip(B.cfd_block_tiles(hs[0]), forms)]
     if profile_steps > 0 and form != "batched":
         for hb in hs:
             B.cfd_profile_reset(hb)
@@ -402,7 +405,7 @@ def main():
     value = head["value"]
     cfg = {k: head[k] for k in ("workload", "blocks", "points", "precision", "form", "cfl", "dt") if k in head}
     cfg.update({"scheme": args.scheme, "parallelism": "single GPU"})
-    for k in ("grid", "tiles", "tuned_tiles"):
+    for k in ("grid", "sweep_forms", "tiles", "tuned_tiles"):
         if k in head:
             cfg[k] = head[k]
     out = {

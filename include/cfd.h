@@ -352,6 +352,15 @@ int cfd_tile_config(int cfg, int* lines, int* nodes, int* threads);
  * the shapes of the first).                                                              */
 int cfd_block_set_tiles(cfd_block* b, const int* cfg);
 int cfd_block_tiles(const cfd_block* b, int* cfg);
+/* Back to the library's own choice (setting the shapes that cfd_block_tiles reports asks for
+ * those shapes in every sweep instead).                                                   */
+int cfd_block_reset_tiles(cfd_block* b);
+/* How the sweep of each direction (forms[0..2] for xi, eta, zeta) runs in an evaluation of all
+ * three with the inviscid terms on: CFD_SWEEP_TILES (the shapes of cfd_block_tiles),
+ * CFD_SWEEP_ROWS (a wavefront per line), CFD_SWEEP_MARCH (a thread per line) or
+ * CFD_SWEEP_ONE_LAUNCH (tiles of all three directions in one launch).                     */
+enum { CFD_SWEEP_TILES = 0, CFD_SWEEP_ROWS = 1, CFD_SWEEP_MARCH = 2, CFD_SWEEP_ONE_LAUNCH = 3 };
+int cfd_block_sweep_forms(const cfd_block* b, int* forms);
 
 /* ---- profiling --------------------------------------------------------------------- */
 /* Enable (1) or disable (0) per-launch HIP event timing of the block's kernels.         */

@@ -23,6 +23,7 @@ CFD_AFWENO_MODIFIED, CFD_AFWENO_ORIGINAL = 0, 1
 CFD_VISC_REFLECT, CFD_VISC_ONE_SIDED = 0, 1
 CFD_BC_PERIODIC, CFD_BC_INTERFACE, CFD_BC_WALL, CFD_BC_FARFIELD, CFD_BC_FARFIELD_CHAR = 0, 1, 2, 3, 4
 CFD_FIELDS_Q, CFD_FIELDS_VISC = 0, 1
+CFD_SWEEP_TILES, CFD_SWEEP_ROWS, CFD_SWEEP_MARCH, CFD_SWEEP_ONE_LAUNCH = 0, 1, 2, 3
 CFD_DIR_XI, CFD_DIR_ETA, CFD_DIR_ZETA, CFD_TERM_INV, CFD_TERM_VIS, CFD_ALL = 1, 2, 4, 8, 16, 31
 
 
@@ -111,6 +112,8 @@ def lib():
         "cfd_tile_config": ([C.c_int, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)], C.c_int),
         "cfd_block_set_tiles": ([_VP, C.POINTER(C.c_int)], C.c_int),
         "cfd_block_tiles": ([_VP, C.POINTER(C.c_int)], C.c_int),
+        "cfd_block_reset_tiles": ([_VP], C.c_int),
+        "cfd_block_sweep_forms": ([_VP, C.POINTER(C.c_int)], C.c_int),
         "cfd_profile_enable": ([_VP, C.c_int], C.c_int),
         "cfd_profile_read": ([_VP, C.POINTER(C.c_char_p), C.POINTER(C.c_int64), _DP, C.c_int, C.POINTER(C.c_int)], C.c_int),
         "cfd_profile_reset": ([_VP], C.c_int),
@@ -361,6 +364,16 @@ def cfd_block_tiles(b: int):
     cfg = (C.c_int * 3)()
     _check(lib().cfd_block_tiles(b, cfg))
     return list(cfg)
+
+
+def cfd_block_reset_tiles(b: int) -> None:
+    _check(lib().cfd_block_reset_tiles(b))
+
+
+def cfd_block_sweep_forms(b: int):
+    forms = (C.c_int * 3)()
+    _check(lib().cfd_block_sweep_forms(b, forms))
+    return list(forms)
 
 
 def cfd_profile_enable(b: int, on: bool = True) -> None:

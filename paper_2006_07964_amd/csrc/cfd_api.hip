@@ -480,6 +480,16 @@ const char* kProfNames[] = {"sweep_xi",    "sweep_eta",    "sweep_zeta",   "swee
                             "sweep_zeta_rk", "visc_prepass", "visc_halo", "halo_q",      "halo_visc",  "sweeps",
                             "sweeps_rk"};
 
+// the three sweeps in one launch, when all run with the inviscid terms
+bool runs_one_launch(const cfd_block* b) { return b->all_sweeps && !b->own_tiles; }
+
+// how a separate launch runs the sweep along dir (partial: into partial sums)
+int sweep_form(const cfd_block* b, int dir, bool inv, bool partial) {
+  if (b->own_tiles || b->d.precision != CFD_FP64 || !inv) return CFD_SWEEP_TILES;
+  if (dir == 0) return CFD_SWEEP_ROWS;
+  return partial && b->march[dir] ? CFD_SWEEP_MARCH : CFD_SWEEP_TILES;
+}
+
 // run the direction sweeps selected by mask; the last one writes R or the RK stage
 // (with_visc: and the viscous prepass before them)
 int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, double* out, const double* qn,
@@ -507,7 +517,7 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
   a.c.ca = ca;
   a.c.cb = cb;
   a.c.cc = cc;
-  const bool one_launch = nd == 3 && inv && b->all_sweeps && !b->own_tiles;  // takes the prepass itself
+  const bool one_launch = nd == 3 && inv && runs_one_launch(b);  // takes the prepass itself
   if (with_visc && vis && !one_launch) {
     const int rc = run_visc(b, Q);
     if (rc) return rc;
@@ -558,15 +568,12 @@ int run_sweeps(cfd_block* b, const double* Q, unsigned mask, int out_kind, doubl
     a.b.out = last ? out : nullptr;
     const char* name = (last && out_kind == kOutRK) ? kSweepRkNames[dirs[n]] : kSweepNames[dirs[n]];
     ProfScope ps(&b->prof, name, b->stream);
-    hipError_t e;
-    if (b->d.precision != CFD_FP64)
-      e = launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
-    else if (!b->own_tiles && dirs[n] == 0 && inv)
-      e = launch_sweep_rows(a, b->stream);
-    else if (!b->own_tiles && b->march[dirs[n]] && inv && !last)
-      e = launch_march(dirs[n], a, b->march[dirs[n]], b->stream);
-    else
-      e = launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
+    const int form = sweep_form(b, dirs[n], inv, !last);
+    const hipError_t e = form == CFD_SWEEP_ROWS    ? launch_sweep_rows(a, b->stream)
+                         : form == CFD_SWEEP_MARCH ? launch_march(dirs[n], a, b->march[dirs[n]], b->stream)
+                         : b->d.precision == CFD_FP64
+                             ? launch_sweep<double>(dirs[n], a, b->stream, b->cfg[dirs[n]])
+                             : launch_sweep<float>(dirs[n], a, b->stream, b->cfg[dirs[n]]);
     ps.done();
     if (e != hipSuccess) return hip_fail(e, "sweep launch");
   }
@@ -685,7 +692,7 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
   b->g.plane = d->ld_i * d->ld_j * (int64_t)(d->nk + 6);
   b->stream = (hipStream_t)hip_stream;
   b->esize = d->precision == CFD_FP64 ? 8 : 4;
-  for (int dir = 0; dir < 3; ++dir) b->cfg[dir] = kDefaultTiles[d->precision == CFD_FP64 ? 0 : 1][dir];
+  (void)cfd_block_reset_tiles(b);
   visc_plan(&b->g, 1, false, d->precision == CFD_FP64, &b->visc_small, &b->visc_kc, &b->visc_tiles);
   for (int dir = 1; dir < 3; ++dir)
     if (d->precision == CFD_FP64 && d->params.weights != CFD_WENO_LINEAR) b->march[dir] = march_len(dir, b->g);
@@ -1836,6 +1843,20 @@ int cfd_block_set_tiles(cfd_block* b, const int* cfg) {
     if (cfg[d] < 0 || cfg[d] >= kTileCfgs) return fail(CFD_ERR_ARG, "tile configuration out of range");
   for (int d = 0; d < 3; ++d) b->cfg[d] = cfg[d];
   b->own_tiles = true;
+  return CFD_OK;
+}
+
+int cfd_block_reset_tiles(cfd_block* b) {
+  if (!b) return fail(CFD_ERR_ARG, "null block");
+  for (int d = 0; d < 3; ++d) b->cfg[d] = kDefaultTiles[b->d.precision == CFD_FP64 ? 0 : 1][d];
+  b->own_tiles = false;
+  return CFD_OK;
+}
+
+int cfd_block_sweep_forms(const cfd_block* b, int* forms) {
+  if (!b || !forms) return fail(CFD_ERR_ARG, "null argument");
+  for (int d = 0; d < 3; ++d)
+    forms[d] = runs_one_launch(b) ? (int)CFD_SWEEP_ONE_LAUNCH : sweep_form(b, d, true, d != kSweepOrder[2]);
   return CFD_OK;
 }
 
