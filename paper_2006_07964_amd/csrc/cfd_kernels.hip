@@ -1882,8 +1882,9 @@ __global__ __launch_bounds__(kMarchNT) __attribute__((amdgpu_waves_per_eu(2, 2))
 // the time of the CU with most workgroups, 15% more where that is one workgroup, whose
 // latencies nothing fills.  The tiles take 46-58 ps per point (eta) and 44-53 (zeta), i.e. a
 // unit per 47000 points.  Measured eta, tiles / march: 96x80x72 31 / 32 us (tiles kept),
-// 160x88x96 64 / 61, 144x120x100 83 / 79, 192x112x72 74 / 69, 128^3 110 / 89, 190x131x93
-// 125 / 103, 256^3 890 / 641.
+// 144x120x100 83 / 79 (tiles kept: 456 workgroups of 16 outputs, two rounds, cost 1% more by the
+// rule), 160x88x96 64 / 61, 192x112x72 74 / 69, 128^3 110 / 89, 190x131x93 125 / 103, 256^3
+// 890 / 641.
 int march_len(int dir, const Geom& g) {
   const int nd = dir == 1 ? g.nj : g.nk, n2 = dir == 1 ? g.nk : g.nj;
   const int64_t groups = ((int64_t)g.ni * n2 + kMarchNT - 1) / kMarchNT;

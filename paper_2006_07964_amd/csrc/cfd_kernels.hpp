@@ -42,6 +42,7 @@ struct ViscArgs {
                   // derivatives use the one-sided closure (the gradients at the three
                   // nodes next to it)
 };
+// viscous prepass of one block; small, a.kc and tiles are those of visc_plan
 template <typename R>
 hipError_t launch_visc(const ViscArgs& a, bool small, int tiles, hipStream_t s);
 // dst[e] = float(src[e]) for e < n
