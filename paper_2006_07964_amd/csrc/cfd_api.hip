@@ -128,6 +128,10 @@ constexpr int kDefaultTiles[2][3] = {{5, 6, 6}, {5, 2, 0}};
 // 254 / 252, 80^3 358 / 376 (the three sets of partial sums are extra traffic); mixed 48^3
 // 115 / 101, 80^3 273 / 267, 96x80x72 281 / 276, 96^3 410 / 423
 constexpr int64_t kAllPoints[2] = {300000, 600000};
+// and whose stored planes are at most this many times that many elements: a small block that lies
+// in the rows and columns of a much larger array would pay gigabytes for the two more sets of
+// partial sums (10 planes; here at most 96 MB)
+constexpr int64_t kAllPitched = 4;
 // largest block, or batch in all, whose viscous prepass runs in that launch too.  RK3 step,
 // prepass before / within: FP64 32^3 74 / 70 us, 48^3 124 / 123, 52x50x52 145 / 148, 64^3
 // 225 / 228 (the sum then gathers 72 flux values per node); mixed 48^3 99 / 92, 64^3 169 / 155,
@@ -361,6 +365,7 @@ BcSeg make_bc(const Geom& G, int blk, int f, int kind) { return make_bc_rect(G, 
 // interior point of every row, element ((k+3)*ld_j + j+3)*ld_i + 3, starts a 128-byte cache
 // line whenever ld_i*esize is a multiple of 128 (the layout callers are advised to use).
 int aligned_planes(size_t plane, int nplanes, size_t esize, void** raw, void** base) {
+  *raw = nullptr;
   const size_t pad = (128 - 3 * esize) / esize;
   if (hipMalloc(raw, (nplanes * plane + pad + 64) * esize) != hipSuccess) return CFD_ERR_ALLOC;
   *base = static_cast<char*>(*raw) + pad * esize;
@@ -710,9 +715,17 @@ int cfd_block_create(const cfd_block_desc* d, void* hip_stream, cfd_block** out)
   if (b->esize != sizeof(double) && aligned_planes(plane, 10 + 9, b->esize, &b->met_r_raw, &b->met_r))
     return cleanup(CFD_ERR_ALLOC, "metrics allocation");
   if (aligned_planes(plane, 12, b->esize, &b->vis_raw, &b->vis)) return cleanup(CFD_ERR_ALLOC, "viscous scratch allocation");
+  const int64_t all_points = kAllPoints[b->esize == sizeof(double) ? 0 : 1];
   b->all_sweeps = d->params.scheme == CFD_AFWENO_MODIFIED && !one_sided_mask(*d) &&
-                  (int64_t)d->ni * d->nj * d->nk <= kAllPoints[b->esize == sizeof(double) ? 0 : 1];
-  if (aligned_planes(plane, b->all_sweeps ? 15 : 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
+                  (int64_t)d->ni * d->nj * d->nk <= all_points && (int64_t)plane <= kAllPitched * all_points;
+  if (b->all_sweeps && aligned_planes(plane, 15, b->esize, &b->rt_raw, &b->rt)) {
+    // not enough memory for three sets of partial sums: the sweeps one by one need one
+    (void)hipGetLastError();
+    (void)hipFree(b->rt_raw);
+    b->rt_raw = nullptr;
+    b->all_sweeps = false;
+  }
+  if (!b->all_sweeps && aligned_planes(plane, 5, b->esize, &b->rt_raw, &b->rt)) return cleanup(CFD_ERR_ALLOC, "partial-sum allocation");
   if (hipMalloc((void**)&b->red_dev, kDtSlots * sizeof(unsigned long long)) != hipSuccess ||
       hipMalloc((void**)&b->flag_dev, sizeof(int)) != hipSuccess || !(b->pin = pin_acquire(b->device)))
     return cleanup(CFD_ERR_ALLOC, "reduction scratch");

@@ -1571,14 +1571,14 @@ template hipError_t launch_combine_batch<float>(bool, const SweepBlock*, const S
 // operands of node p+1 are requested before the arithmetic of node p, which takes several
 // memory latencies.
 //
-// Why: the tile kernel is bound by FP64 issue (SIMDs 80-88% busy at the clock the chip holds
-// under this load, about 1.7 GHz) and spends 1036 VALU instructions per point on rows it
-// recomputes (WENO 32/30, nodal fluxes 36/30, half-point metrics twice), projections of
-// states instead of differences and tile addressing; this form takes 740, a quarter of the
-// LDS instructions and reads Q once.  Two waves per SIMD with 230-254 VGPRs: the outputs in
-// flight and the node's basis do not fit less, and the SIMDs are 88-92% busy.
-// Measured, 512 x 512 x 384: zeta 4.47 -> 3.41 ms, eta 4.78 -> 3.71 ms (17.7 GB at 95% of the
-// rate of a device copy); 160^3 193 -> 153 us and 239 -> 168 us.
+// Why: the tile kernels issue VALU work on 76% of the cycles of the clock that the chip holds
+// under this load (1.76-1.87 GHz), 936 (zeta) and 970 (eta) instructions per point, on rows that
+// they recompute (WENO 32/30, nodal fluxes 36/30, half-point metrics twice) and on tile
+// addressing; this form takes 725, a quarter of the LDS instructions and reads Q once.  Two waves
+// per SIMD with 230-254 VGPRs: the outputs in flight and the node's basis do not fit less.  It
+// issues on 70-77% of the cycles and moves its bytes at 83-90% of the rate of a device copy.
+// Measured, 512 x 512 x 384: zeta 4.26 -> 3.31 ms, eta 4.64 -> 3.90 ms; 160^3 193 -> 153 us and
+// 239 -> 168 us.
 //
 // The original scheme walks the same way with one slot more: node p completes the stencil
 // p-5 .. p of the half point p-5/2, whose flux goes to outputs p-3 and p-2 at once (160^3 eta
