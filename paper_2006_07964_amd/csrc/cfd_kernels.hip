@@ -1576,7 +1576,7 @@ template hipError_t launch_combine_batch<float>(bool, const SweepBlock*, const S
 // they recompute (WENO 32/30, nodal fluxes 36/30, half-point metrics twice) and on tile
 // addressing; this form takes 725, a quarter of the LDS instructions and reads Q once.  Two waves
 // per SIMD with 230-254 VGPRs: the outputs in flight and the node's basis do not fit less.  It
-// issues on 70-77% of the cycles and moves its bytes at 83-90% of the rate of a device copy.
+// issues on 70-78% of the cycles and moves its bytes at 83-90% of the rate of a device copy.
 // Measured, 512 x 512 x 384: zeta 4.26 -> 3.31 ms, eta 4.64 -> 3.90 ms; 160^3 193 -> 153 us and
 // 239 -> 168 us.
 //
